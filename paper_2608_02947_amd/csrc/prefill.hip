@@ -61,6 +61,7 @@
 #include "atf_internal.hpp"
 #include "rope.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace atf {
@@ -758,17 +759,349 @@ prefill_kernel(const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p
             m_run * 0.69314718055994531f + logf(l_tot);
 }
 
-template <int D, bool kRot, class P>
-hipError_t launch_d(const P& p, unsigned blocks, bool window_on, hipStream_t stream) {
-    constexpr unsigned kLdsOn = kRot ? RotLds<D, true>::kBytes : 0u;
-    constexpr unsigned kLdsOff = kRot ? RotLds<D, false>::kBytes : 0u;
-    if (window_on)
-        hipLaunchKernelGGL((prefill_kernel<D, true, kRot>), dim3(blocks), dim3(Cfg<D, true>::kThreads),
-                           kLdsOn, stream, p);
-    else
-        hipLaunchKernelGGL((prefill_kernel<D, false, kRot>), dim3(blocks),
-                           dim3(Cfg<D, false>::kThreads), kLdsOff, stream, p);
-    return hipGetLastError();
+// ---- Calls with few rows: the keys of a row block split over the waves of its workgroup.
+//
+// prefill_kernel gives a CU 256 rows (128 at d = 64), so a call with few rows (an
+// appended turn, a short prompt) leaves most of the chip idle while a few workgroups
+// walk all the keys.  Here a workgroup owns ONE block of 32 rows and its S waves
+// take the 32-key blocks u = wave, wave + S, ..., each with its own softmax state; the
+// states are merged in LDS at the end, in wave order.  The waves share nothing while
+// they stream, so there is no LDS staging and no barrier: operand fragments are 16-byte
+// loads from the caches into registers (the decode kernel's form), a block's V issued
+// before its QK and the next block's K after it.
+//
+// What bounds it: every row block reads its keys through L1 by itself (8 to 16 KB per 32
+// keys against 64 B per clock), which costs more than the matrix work once every CU is
+// full; a row costs about 1.5 times what it does in prefill_kernel, and `short_split`
+// takes this kernel only where the idle CUs cost more.  Chunks that no cell keeps are not
+// loaded (a fixed number of loads, the pruned ones out of a buffer's range, took 1.3 times
+// as long with every CU full).  Measured, windowed, prefill_kernel -> this one: 300 rows
+// against 65,836 keys (28 heads on 4, d = 128) 1310 -> 508 us; 16 rows against 20,000 keys
+// 321 -> 89 us, at d = 64 239 -> 54 us; a 1,024-token prompt (14 heads on 2, d = 64)
+// 28.8 -> 11.4 us.
+// Slower: K staged through a per-wave LDS ring (501 us at the 300 rows), two row blocks
+// sharing staged tiles of 128 keys with a barrier each (489 us; 184 us at the 16 rows),
+// 64 rows per wave with 512 registers (1450 us, spilled).
+//
+// Rows are grouped as in prefill_kernel (the same position tiles, the same 32 rows to a
+// wave) and a block of keys belongs to the same wave whatever n_q is, so chunks of a
+// prefill that take this kernel with the same S agree bit for bit.
+//
+// kRot: queries rotated as they are loaded, the kept chunks of a block's keys in
+// registers before their products; angles as in the decode kernel (the block's first
+// position, evaluated by lane r for pair r, plus the offset's table entry).
+template <int D, bool kWin, bool kRot, int S>
+__global__ __launch_bounds__(S * 64, 2) void prefill_short_kernel(
+    const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p) {
+    constexpr int kChunks = D / 16;
+    constexpr int kHalf = D / 2;
+    constexpr int kDB = D / 32;
+    constexpr int kBlk = 32;  // keys per step of a wave
+    constexpr int kVBlkBytes = D * 32;
+    constexpr int kParts = Cfg<D, kWin>::kRows / 32;  // row blocks per position tile
+    constexpr int kCStride = D + 4;
+    __shared__ float red_m[S][32];
+    __shared__ float red_l[S][32];
+    // While the waves stream: the queries, then (rotation) the (cos, sin) of col * theta_r
+    // for the 32 key offsets of a block, rows padded by 16 bytes, and per wave those of the
+    // block's first position * theta_r.  Afterwards: the waves' weighted outputs.
+    constexpr int kTables = 16 * D + (kRot ? 32 * kCStride + S * D : 0);  // floats
+    constexpr int kMerge = S * 32 * (D + 1);
+    __shared__ __attribute__((aligned(16))) float shared[kTables > kMerge ? kTables : kMerge];
+    uint16_t* const Qs = reinterpret_cast<uint16_t*>(shared);
+    float* const s_colcs = shared + 16 * D;
+    float* const s_blkcs = s_colcs + 32 * kCStride;
+    float* const red_o = shared;  // [S][32][D + 1]
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31;
+    const int hh = lane >> 5;
+
+    // block -> (position tile, row block, kv head, batch), late rows first; heads vary
+    // fastest, as in prefill_kernel, so that each XCD keeps to fixed KV heads
+    const int per_tile = p.h_kv * p.batch;
+    const int rem = blockIdx.x % per_tile;
+    const int tb = blockIdx.x / per_tile;
+    const int qt = p.n_qtiles - 1 - tb / kParts;
+    const int row0 = 32 * (kParts - 1 - tb % kParts);
+    const int g = rem % p.h_kv;
+    const int b = rem / p.h_kv;
+    const int G = p.group;
+
+    const int i0 = qt * p.pos_per_tile;
+    const int rows_valid = min(p.pos_per_tile, p.n_q - i0) * G;
+    if (row0 >= rows_valid) return;  // the whole workgroup
+    const int pos0 = p.q_pos0 + i0;
+    const int my_pos = pos0 + min(row0 + col, rows_valid - 1) / G;
+    const int wp_min = pos0 + row0 / G;
+    const int wp_max = pos0 + min(row0 + 31, rows_valid - 1) / G;
+    const int n_blk = __builtin_amdgcn_readfirstlane((min(p.n_k, wp_max + 1) + kBlk - 1) / kBlk);
+    const int my_w = lane < kHalf ? p.win.W[lane] : -1;
+
+    const int64_t chunk_bytes = int64_t(p.cache_tokens) * 32;
+    const char* kpcm = reinterpret_cast<const char*>(p.k) + (int64_t(b) * p.h_kv + g) * kChunks * chunk_bytes;
+    const int n_vblk = (p.cache_tokens + 15) / 16;
+    const char* vhead = reinterpret_cast<const char*>(p.v) + (int64_t(b) * p.h_kv + g) * n_vblk * int64_t(kVBlkBytes);
+    const uint32_t piece = uint32_t(col * 32 + hh * 16);
+
+    // The row block's queries: chunk c, half h, row r at 1024 c + 512 h + 16 r (each wave
+    // writes whole chunks, lane = (half, row))
+    for (int e = tid; e < kChunks * 64; e += S * 64) {
+        const int c = __builtin_amdgcn_readfirstlane(e >> 6), fr = row0 + col;
+        u32x4_t z = {0u, 0u, 0u, 0u};
+        if (fr < rows_valid)
+            z = *reinterpret_cast<const u32x4_t*>(p.q + ((int64_t(b) * p.n_q + i0 + fr / G) * p.h_q + g * G + fr % G) * D +
+                                                  hh * kHalf + 8 * c);
+        if constexpr (kRot)
+            z = rope::rotate(z, rope::other_half(z, hh), hh, uint32_t(my_pos), &p.rope_rho_hi[8 * c],
+                             &p.rope_rho_lo[8 * c]);
+        *reinterpret_cast<u32x4_t*>(&Qs[8 * e]) = z;
+    }
+    uint2 my_rho = make_uint2(0u, 0u);  // lane r: the rotation fraction of pair r
+    if constexpr (kRot) {
+        for (int e = tid; e < 32 * kHalf; e += S * 64) {
+            const int kk = e / kHalf, r = e % kHalf;
+            const float u = rope::revolutions(uint32_t(kk), make_uint2(p.rope_rho_hi[r], p.rope_rho_lo[r]));
+            s_colcs[kk * kCStride + 2 * r] = __builtin_amdgcn_cosf(u);
+            s_colcs[kk * kCStride + 2 * r + 1] = __builtin_amdgcn_sinf(u);
+        }
+        if (lane < kHalf) my_rho = make_uint2(p.rope_rho_hi[lane], p.rope_rho_lo[lane]);
+    }
+    __syncthreads();
+    const uint32_t q_lane = lds_addr(Qs) + uint32_t(hh * 512 + col * 16);
+    auto q_frag = [&](int c) __attribute__((always_inline)) { return lds_read_b128(q_lane + 1024u * c); };
+
+    f32x16_t oacc[kDB];
+#pragma unroll
+    for (int i = 0; i < kDB; ++i) oacc[i] = zero16();
+    float m_run = -INFINITY, m_thr = -INFINITY, m_neg = 0.f, l_run = 0.f;
+    const float sc = p.scale_log2;
+
+    // the window's classification of block u: `full` = pairs kept in every cell, `keep` =
+    // pairs kept in some cell (lane r holds W_r)
+    auto classify = [&](int u, uint64_t& full, uint64_t& keep) __attribute__((always_inline)) {
+        if constexpr (kWin) {
+            full = __ballot(my_w >= wp_max - u * kBlk);
+            keep = __ballot(my_w >= max(0, wp_min - (u * kBlk + kBlk - 1)));
+        } else {
+            full = keep = ~0ull;
+        }
+    };
+    // K fragments of block u (A operand: key 32 u + col, half hh of every kept chunk; the
+    // last chunk is always multiplied).  One scalar base per block and fixed 32-bit lane
+    // offsets (the host checks that the chunks' span fits); keys past n_k - 1 read that key
+    // and are masked.
+    u32x4_t kf[kChunks];
+    uint32_t k_off[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) k_off[c] = uint32_t(c) * uint32_t(chunk_bytes) + piece;
+    auto load_k = [&](int u, uint64_t keep) __attribute__((always_inline)) {
+        const int jb = u * kBlk;
+        const char* base = kpcm + int64_t(jb) * 32;
+        const uint32_t back = jb + kBlk <= p.n_k ? 0u : uint32_t(max(0, col - (p.n_k - 1 - jb))) * 32u;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c)
+            if (!kWin || c == kChunks - 1 || ((keep >> (8 * c)) & 0xFFull))
+                kf[c] = *reinterpret_cast<const u32x4_t*>(base + (k_off[c] - back));
+    };
+
+    // query operands with the dims of the pairs outside qf_full zeroed: remade where a
+    // threshold enters or leaves the block's distances
+    uint64_t full = 0, keep = 0, qf_full = kWin ? 0 : ~0ull;
+    u32x4_t qf[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) qf[c] = kWin ? u32x4_t{0u, 0u, 0u, 0u} : q_frag(c);
+    if (wave < n_blk) {
+        classify(wave, full, keep);
+        load_k(wave, keep);
+    }
+    for (int u = wave; u < n_blk; u += S) {
+        const int jb = u * kBlk;
+        // V^T fragments (A operand: dim 32 i + col, half hh of each 16-token block; blocks
+        // past the last key re-read the last block and are zeroed below)
+        u32x4_t vf[2][kDB];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const char* vb = vhead + int64_t(min(2 * u + ks, (p.n_k - 1) / 16)) * kVBlkBytes;
+#pragma unroll
+            for (int i = 0; i < kDB; ++i) vf[ks][i] = *reinterpret_cast<const u32x4_t*>(vb + 1024 * i + piece);
+        }
+        if constexpr (kRot) {
+            const float ub = rope::revolutions(uint32_t(jb), my_rho);
+            float* const blk = &s_blkcs[wave * D];
+            if (lane < kHalf) {
+                blk[2 * lane] = __builtin_amdgcn_cosf(ub);
+                blk[2 * lane + 1] = __builtin_amdgcn_sinf(ub);
+            }
+            // the wave's own LDS writes complete before its later LDS reads; the fences keep
+            // the compiler from moving the reads above the writes
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int c = 0; c < kChunks; ++c) {
+                if (!kWin || c == kChunks - 1 || ((keep >> (8 * c)) & 0xFFull))
+                    kf[c] = rope::rotate_block(kf[c], hh, &s_colcs[col * kCStride + 16 * c], blk + 16 * c);
+                __builtin_amdgcn_sched_barrier(0);  // one chunk's angles at a time in registers
+            }
+        }
+        f32x16_t sacc;  // QK, lowest frequencies first
+        if constexpr (kWin) {
+            if (full != qf_full) {
+                qf_full = full;
+#pragma unroll
+                for (int c = 0; c < kChunks; ++c)
+                    qf[c] = keep_pairs(q_frag(c), uint32_t(full >> (8 * c)) & 0xFFu);
+            }
+        }
+#pragma unroll
+        for (int c = kChunks - 1; c >= 0; --c) {
+            if (c == kChunks - 1)
+                sacc = mfma(kf[c], qf[c], zero16());
+            else if (!kWin || ((full >> (8 * c)) & 0xFFull))
+                sacc = mfma(kf[c], qf[c], sacc);
+        }
+        if constexpr (kWin) {
+            // pairs whose window ends inside the block, grouped by chunk and threshold: one
+            // MFMA per group, added where z <= W_r
+            uint64_t part = keep & ~full;
+            while (part) {
+                const int r = __builtin_ctzll(part);
+                const int c = r >> 3;
+                const int wr = __builtin_amdgcn_readlane(my_w, r);
+                const uint64_t grp = __ballot(my_w == wr) & part & (0xFFull << (8 * c));
+                part &= ~grp;
+                u32x4_t kc = kf[0];
+#pragma unroll
+                for (int cc = 1; cc < kChunks; ++cc)
+                    if (cc == c) kc = kf[cc];
+                const f32x16_t pr = mfma(kc, keep_pairs(q_frag(c), uint32_t(grp >> (8 * c))), zero16());
+                const int thr = my_pos - jb - 4 * hh - wr;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int off = 8 * (v / 4) + (v % 4);
+                    sacc[v] += off >= thr ? pr[v] : 0.f;
+                }
+            }
+        }
+        {
+            // the wave's next block (past its last one: this block again, unused)
+            const int un = u + S < n_blk ? u + S : u;
+            classify(un, full, keep);
+            load_k(un, keep);
+        }
+        if (jb + kBlk > p.n_k) {
+            // V slots of keys at or past n_k: zero (the cache there may hold anything, and a
+            // zero probability does not cancel a NaN in the matrix product)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const int lim = p.n_k - jb - 16 * ks - 4 * hh;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int e0 = 2 * t, e1 = 2 * t + 1;
+                    const uint32_t m = (8 * (e0 / 4) + e0 % 4 < lim ? 0x0000FFFFu : 0u) |
+                                       (8 * (e1 / 4) + e1 % 4 < lim ? 0xFFFF0000u : 0u);
+#pragma unroll
+                    for (int i = 0; i < kDB; ++i) vf[ks][i][t] &= m;
+                }
+            }
+        }
+        if (wp_min < jb + kBlk - 1 || jb + kBlk > p.n_k) {
+            // cell kept iff off <= lim; see softmax_pv of prefill_kernel
+            const int lim = min(my_pos - jb, p.n_k - 1 - jb) - 4 * hh;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int off = 8 * (v / 4) + (v % 4);
+                const uint32_t inf = (uint32_t(lim - off) & 0x80000000u) | 0x7F800000u;
+                sacc[v] = fminf(sacc[v], __uint_as_float(inf));
+            }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+        if (__any(mx * sc > m_thr)) {
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m_run, mx * sc);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = exp2_fast(m_run - m_use);
+            m_run = m_new;
+            m_thr = m_new + kRescale;
+            m_neg = -m_use;
+            l_run *= alpha;
+#pragma unroll
+            for (int i = 0; i < kDB; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) oacc[i][v] *= alpha;
+        }
+        u32x4_t pb[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float a = exp2_fast(__builtin_fmaf(sacc[8 * ks + 2 * t], sc, m_neg));
+                const float c2 = exp2_fast(__builtin_fmaf(sacc[8 * ks + 2 * t + 1], sc, m_neg));
+                l_run += a;
+                l_run += c2;
+                bf16x2_t two;
+                two[0] = (__bf16)a;
+                two[1] = (__bf16)c2;
+                pb[ks][t] = __builtin_bit_cast(uint32_t, two);
+            }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < kDB; ++i) oacc[i] = mfma(vf[ks][i], pb[ks], oacc[i]);
+    }
+
+    // ---- merge the waves' states in wave order: weights 2^(m_w - M) from all maxima, each
+    // wave's weighted output in an LDS slab of its own, then S values summed per output
+    const float l_lane = l_run + __shfl_xor(l_run, 32);
+    if (hh == 0) {
+        red_m[wave][col] = m_run;
+        red_l[wave][col] = l_lane;
+    }
+    __syncthreads();
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < S; ++w) M = fmaxf(M, red_m[w][col]);
+    const float wt = m_run == -INFINITY ? 0.f : exp2_fast(m_run - M);
+#pragma unroll
+    for (int i = 0; i < kDB; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            red_o[(32 * wave + col) * (D + 1) + 32 * i + 8 * (v / 4) + 4 * hh + (v % 4)] = oacc[i][v] * wt;
+    __syncthreads();
+    for (int e = tid; e < 32 * (D / 8); e += S * 64) {
+        const int r = e / (D / 8), x0 = 8 * (e % (D / 8));
+        const int fr = row0 + r;
+        if (fr >= rows_valid) break;
+        float Mr = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < S; ++w) Mr = fmaxf(Mr, red_m[w][r]);
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < S; ++w)
+            L += red_m[w][r] == -INFINITY ? 0.f : red_l[w][r] * exp2_fast(red_m[w][r] - Mr);
+        const float inv = 1.0f / L;
+        u32x4_t out;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            bf16x2_t two;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float a = 0.f;
+#pragma unroll
+                for (int w = 0; w < S; ++w) a += red_o[(32 * w + r) * (D + 1) + x0 + 2 * t + h];
+                two[h] = (__bf16)(a * inv);
+            }
+            out[t] = __builtin_bit_cast(uint32_t, two);
+        }
+        const int qrow = i0 + fr / G, head = g * G + fr % G;
+        *reinterpret_cast<u32x4_t*>(p.o + ((int64_t(b) * p.n_q + qrow) * p.h_q + head) * D + x0) = out;
+        if (x0 == 0) p.lse[(int64_t(b) * p.h_q + head) * p.n_q + qrow] = Mr * 0.69314718055994531f + logf(L);
+    }
 }
 
 // Tile geometry and the uniform-run test, shared by both launchers.
@@ -796,6 +1129,68 @@ hipError_t prepare(P& p, int head_dim, unsigned* blocks, bool* window_on) {
     *window_on = on;
     (void)hipGetLastError();
     return hipSuccess;
+}
+
+
+// Waves per row block of prefill_short_kernel for this call, or 0 for prefill_kernel.
+//
+// prefill_kernel takes as long as its longest row as long as its workgroups (`blocks` of
+// them) do not fill the chip; the short kernel takes as long as the keys of all its row
+// blocks together.  So the line lies on x = blocks * (mean keys of a row / keys of the
+// longest row): the short kernel's gain, prefill_kernel's time over its own, falls with x
+// and passes 1 at (measured over 28/4, 24/8 (d = 128), 14/2 and 16/16 heads (d = 64), 64
+// to 5,000 rows, 512 to 40,000 keys)
+//   d = 128, windowed: 1.30 at x = 97..116, 1.04-1.18 at 132..145, 0.93-1.06 at 146..173
+//   d = 128, off:      1.17-1.18 at 98..116, 0.96-1.09 at 120..132, 0.82-0.95 at 146..173
+//   d = 64, windowed (128-row workgroups): 1.26 at 241, 1.23-1.29 at 278..320
+//   d = 64, off: 1.43 at 139, 1.28 at 160
+// and where keys are rotated as they are read (every row block turns its own keys)
+//   d = 128: windowed 1.29-1.55 at 52..63, 0.80-1.02 at 84..98; off 1.03-1.11 at 52..58,
+//   0.79-0.90 at 67..72;  d = 64: windowed 1.14-1.63 at 167..200, 0.90-1.03 at 223..241;
+//   off 1.05-1.19 at 78..84, 0.84-1.04 at 96..112
+// Eight waves instead of four halve the row block's time while every row block has a CU
+// to itself (8 waves of its registers fill one): 256 row blocks or fewer (300 rows of
+// 24/8 heads against 8,000 keys 64 -> 49 us; 64 rows against 8,000 keys 58 -> 43 us).
+// Below about 4,096 keys the merge of the longer list of states takes the gain back (512
+// keys: equal).
+int short_split(const PrefillParams& p, int head_dim, bool window_on, bool rotate, int64_t blocks) {
+    // the short kernel's lane offsets cover all chunks of a token's stream in 32 bits
+    if (int64_t(p.cache_tokens) * head_dim * 2 > int64_t(UINT32_MAX)) return 0;
+    const int64_t longest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + p.n_q);
+    const int64_t shortest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + 1);
+    const int64_t limit = head_dim == 64 ? (window_on ? (rotate ? 192 : 320) : (rotate ? 80 : 160))
+                                         : (rotate ? (window_on ? 64 : 56) : (window_on ? 132 : 120));
+    if (blocks * ((shortest + longest) / 2) > limit * longest) return 0;
+    const int64_t row_blocks = blocks * (head_dim == 64 && window_on ? 4 : 8);
+    return row_blocks <= 256 && longest >= 4096 ? 8 : 4;
+}
+
+template <int D, bool kWin, bool kRot, class P>
+hipError_t launch_short(const P& p, int64_t blocks, int S, hipStream_t stream) {
+    const int64_t n = blocks * (Cfg<D, kWin>::kRows / 32);
+    if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
+    if (S == 8)
+        hipLaunchKernelGGL((prefill_short_kernel<D, kWin, kRot, 8>), dim3(unsigned(n)), dim3(512), 0, stream, p);
+    else
+        hipLaunchKernelGGL((prefill_short_kernel<D, kWin, kRot, 4>), dim3(unsigned(n)), dim3(256), 0, stream, p);
+    return hipGetLastError();
+}
+
+template <int D, bool kRot, class P>
+hipError_t launch_d(const P& p, unsigned blocks, bool window_on, hipStream_t stream) {
+    const int split = short_split(p, D, window_on, kRot, blocks);
+    if (split)
+        return window_on ? launch_short<D, true, kRot>(p, blocks, split, stream)
+                         : launch_short<D, false, kRot>(p, blocks, split, stream);
+    constexpr unsigned kLdsOn = kRot ? RotLds<D, true>::kBytes : 0u;
+    constexpr unsigned kLdsOff = kRot ? RotLds<D, false>::kBytes : 0u;
+    if (window_on)
+        hipLaunchKernelGGL((prefill_kernel<D, true, kRot>), dim3(blocks), dim3(Cfg<D, true>::kThreads),
+                           kLdsOn, stream, p);
+    else
+        hipLaunchKernelGGL((prefill_kernel<D, false, kRot>), dim3(blocks),
+                           dim3(Cfg<D, false>::kThreads), kLdsOff, stream, p);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -74,5 +74,26 @@ __device__ __forceinline__ u32x4_t other_half(u32x4_t x, int hh) {
     return r;
 }
 
+// Rotate one fragment of a 32-token block by angle addition: `colcs` the (cos, sin) of the
+// token's offset in the block, `blkcs` of the block's first position, for the fragment's 8
+// pairs (16-byte aligned).  Every lane of the wave must execute it.
+__device__ __forceinline__ u32x4_t rotate_block(u32x4_t own, int hh, const float* colcs, const float* blkcs) {
+    float cs8[8], sn8[8];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 v = *reinterpret_cast<const float4*>(colcs + 4 * q4);  // pairs 2q4, 2q4+1
+        const float4 w = *reinterpret_cast<const float4*>(blkcs + 4 * q4);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int e = 2 * q4 + j;
+            const float cB = j ? w.z : w.x, sB = j ? w.w : w.y;
+            const float cC = j ? v.z : v.x, sC = j ? v.w : v.y;
+            cs8[e] = __builtin_fmaf(cB, cC, -sB * sC);
+            sn8[e] = __builtin_fmaf(sB, cC, cB * sC);
+        }
+    }
+    return rotate_cs(own, other_half(own, hh), hh, cs8, sn8);
+}
+
 }  // namespace rope
 }  // namespace atf

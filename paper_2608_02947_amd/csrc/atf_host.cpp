@@ -416,9 +416,13 @@ int atf_pack_kcache(const void* k_bshd, void* k_pcm, int32_t batch, int64_t n_k,
     const size_t bytes = size_t(batch) * size_t(n_k) * size_t(h_kv) * size_t(head_dim) * 2;
     int rc = check_pack("pack_kcache", k_bshd, k_pcm, batch, n_k, h_kv, head_dim, bytes);
     if (rc != ATF_OK) return rc;
-    atf::PackParams p{static_cast<const uint16_t*>(k_bshd), static_cast<uint16_t*>(k_pcm), batch,
-                      static_cast<int32_t>(n_k), h_kv, 0, static_cast<int32_t>(n_k), 0};
-    hipError_t e = atf::launch_pack_kcache(p, head_dim, static_cast<hipStream_t>(hip_stream));
+    atf::AppendParams p{};
+    p.k_src = static_cast<const uint16_t*>(k_bshd);
+    p.k_dst = static_cast<uint16_t*>(k_pcm);
+    p.batch = batch;
+    p.n_new = p.cache_tokens = static_cast<int32_t>(n_k);
+    p.h_kv = h_kv;
+    hipError_t e = atf::launch_append(p, false, head_dim, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return fail(ATF_EHIP, "pack_kcache: launch failed: %s", hipGetErrorString(e));
     return ATF_OK;
 }
@@ -474,9 +478,14 @@ int atf_pack_vcache(const void* v_bshd, void* v_pack, int32_t batch, int64_t n_k
                         (batch >= 1 && n_k >= 1 && h_kv >= 1 && n_k <= kPosLimit)
                             ? vcache_bytes(batch, n_k, h_kv, head_dim) : 0);
     if (rc != ATF_OK) return rc;
-    atf::PackParams p{static_cast<const uint16_t*>(v_bshd), static_cast<uint16_t*>(v_pack), batch,
-                      static_cast<int32_t>(n_k), h_kv, 0, static_cast<int32_t>(n_k), 1};
-    hipError_t e = atf::launch_pack_vcache(p, head_dim, static_cast<hipStream_t>(hip_stream));
+    atf::AppendParams p{};
+    p.v_src = static_cast<const uint16_t*>(v_bshd);
+    p.v_dst = static_cast<uint16_t*>(v_pack);
+    p.batch = batch;
+    p.n_new = p.cache_tokens = static_cast<int32_t>(n_k);
+    p.h_kv = h_kv;
+    p.zero_tail = 1;
+    hipError_t e = atf::launch_append(p, false, head_dim, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return fail(ATF_EHIP, "pack_vcache: launch failed: %s", hipGetErrorString(e));
     return ATF_OK;
 }
@@ -487,7 +496,7 @@ namespace {
 int cache_append_impl(const char* fn, const void* k_new, const void* v_new, void* k_cache,
                       void* v_cache, int32_t batch, int64_t n_new, int64_t pos0, int32_t h_kv,
                       int32_t head_dim, int64_t cache_tokens, void* hip_stream,
-                      const atf::RotateParams* rope) {
+                      const atf::AppendParams* rope) {
     if (head_dim != 64 && head_dim != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built", fn, head_dim);
     if (batch < 1 || h_kv < 1 || n_new < 0 || pos0 < 0 || cache_tokens < 1 ||
@@ -510,30 +519,17 @@ int cache_append_impl(const char* fn, const void* k_new, const void* v_new, void
             if (bufs[i] < bufs[j] + sizes[j] && bufs[j] < bufs[i] + sizes[i])
                 return fail(ATF_EINVAL, "%s: buffers overlap", fn);
     if (n_new == 0) return ATF_OK;
-    const hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    atf::PackParams pk{static_cast<const uint16_t*>(k_new), static_cast<uint16_t*>(k_cache), batch,
-                       static_cast<int32_t>(n_new), h_kv, static_cast<int32_t>(pos0),
-                       static_cast<int32_t>(cache_tokens), 0};
-    hipError_t e;
-    if (rope != nullptr) {
-        atf::RotateParams rp = *rope;
-        rp.src = pk.src;
-        rp.dst = pk.dst;
-        rp.batch = batch;
-        rp.n_k = pk.n_k;
-        rp.h_kv = h_kv;
-        rp.cache_tokens = pk.cache_tokens;
-        rp.pos0 = pk.pos0;
-        e = atf::launch_append_rotated_k(rp, head_dim, st);
-    } else {
-        e = atf::launch_pack_kcache(pk, head_dim, st);
-    }
-    if (e == hipSuccess) {
-        atf::PackParams pv = pk;
-        pv.src = static_cast<const uint16_t*>(v_new);
-        pv.dst = static_cast<uint16_t*>(v_cache);
-        e = atf::launch_pack_vcache(pv, head_dim, st);
-    }
+    atf::AppendParams p = rope != nullptr ? *rope : atf::AppendParams{};
+    p.k_src = static_cast<const uint16_t*>(k_new);
+    p.v_src = static_cast<const uint16_t*>(v_new);
+    p.k_dst = static_cast<uint16_t*>(k_cache);
+    p.v_dst = static_cast<uint16_t*>(v_cache);
+    p.batch = batch;
+    p.n_new = static_cast<int32_t>(n_new);
+    p.h_kv = h_kv;
+    p.pos0 = static_cast<int32_t>(pos0);
+    p.cache_tokens = static_cast<int32_t>(cache_tokens);
+    const hipError_t e = atf::launch_append(p, rope != nullptr, head_dim, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return fail(ATF_EHIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
     return ATF_OK;
 }
@@ -555,7 +551,7 @@ int atf_cache_append_rotated(const void* k_new, const void* v_new, void* k_cache
     const int d = w->head_dim;
     if (d != 64 && d != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built (64 or 128)", fn, d);
-    atf::RotateParams rp{};
+    atf::AppendParams rp{};
     const int rc = rope_fractions(fn, w, rope_inv_freq, rp.rope_rho_hi, rp.rope_rho_lo);
     if (rc != ATF_OK) return rc;
     return cache_append_impl(fn, k_new, v_new, k_cache, v_cache, batch, n_new, pos0, h_kv, d,
@@ -874,7 +870,7 @@ int cache_append_paged_impl(const char* fn, const void* k_new, const void* v_new
                             void* v_pages, const int32_t* block_table, int32_t max_pages_per_row,
                             int32_t num_pages, int32_t page_tokens, int32_t batch, int64_t n_new,
                             int64_t pos0, int32_t h_kv, int32_t head_dim, void* hip_stream,
-                            const atf::RotatePagedParams* rope) {
+                            const atf::AppendParams* rope) {
     if (head_dim != 64 && head_dim != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built", fn, head_dim);
     if (batch < 1 || h_kv < 1 || n_new < 0 || pos0 < 0)
@@ -896,11 +892,11 @@ int cache_append_paged_impl(const char* fn, const void* k_new, const void* v_new
     if (n_new == 0) return ATF_OK;
     if (int64_t(batch) * n_new * h_kv > kPosLimit)
         return fail(ATF_EINVAL, "%s: too many tokens for one call", fn);
-    atf::AppendPagedParams p{};
+    atf::AppendParams p = rope != nullptr ? *rope : atf::AppendParams{};
     p.k_src = static_cast<const uint16_t*>(k_new);
     p.v_src = static_cast<const uint16_t*>(v_new);
-    p.k_pages = static_cast<uint16_t*>(k_pages);
-    p.v_pages = static_cast<uint16_t*>(v_pages);
+    p.k_dst = static_cast<uint16_t*>(k_pages);
+    p.v_dst = static_cast<uint16_t*>(v_pages);
     p.block_table = block_table;
     p.batch = batch;
     p.n_new = static_cast<int32_t>(n_new);
@@ -909,14 +905,7 @@ int cache_append_paged_impl(const char* fn, const void* k_new, const void* v_new
     p.max_pages = max_pages_per_row;
     p.num_pages = num_pages;
     p.page_tokens = page_tokens;
-    hipError_t e;
-    if (rope != nullptr) {
-        atf::RotatePagedParams rp = *rope;
-        rp.a = p;
-        e = atf::launch_append_paged_rotated(rp, head_dim, static_cast<hipStream_t>(hip_stream));
-    } else {
-        e = atf::launch_append_paged(p, head_dim, static_cast<hipStream_t>(hip_stream));
-    }
+    const hipError_t e = atf::launch_append(p, rope != nullptr, head_dim, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return fail(ATF_EHIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
     return ATF_OK;
 }
@@ -942,7 +931,7 @@ int atf_cache_append_paged_rotated(const void* k_new, const void* v_new, void* k
     const int d = w->head_dim;
     if (d != 64 && d != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built (64 or 128)", fn, d);
-    atf::RotatePagedParams rp{};
+    atf::AppendParams rp{};
     const int rc = rope_fractions(fn, w, rope_inv_freq, rp.rope_rho_hi, rp.rope_rho_lo);
     if (rc != ATF_OK) return rc;
     return cache_append_paged_impl(fn, k_new, v_new, k_pages, v_pages, block_table,

@@ -81,42 +81,30 @@ struct DecodeParams {
     uint32_t rope_rho_lo[kMaxPairs];
 };
 
-struct AppendPagedParams {
-    const uint16_t* k_src;     // [B][n_new][h_kv][d]: tokens pos0 .. pos0 + n_new - 1
+// Append of n_new tokens at cache positions pos0 .. (rotate.hip): a NULL k_src or v_src
+// leaves that cache alone (the packs).
+struct AppendParams {
+    const uint16_t* k_src;       // [B][n_new][h_kv][d]
     const uint16_t* v_src;
-    uint16_t* k_pages;         // [num_pages][h_kv][d/16][page_tokens][16]
-    uint16_t* v_pages;         // [num_pages][h_kv][page_tokens/16][d][16]
-    const int32_t* block_table;  // [B][max_pages]
-    int32_t batch, n_new, pos0, h_kv, max_pages, num_pages, page_tokens;
-};
-
-// The paged append with RoPE on the way in (rotate.hip): AppendPagedParams' fields, and
-// the rotation's 0.64 fixed-point frequencies.
-struct RotatePagedParams {
-    AppendPagedParams a;
-    uint32_t rope_rho_hi[kMaxPairs];
+    uint16_t* k_dst;             // [B][h_kv][d/16][cache_tokens][16], or pages
+                                 // [num_pages][h_kv][d/16][page_tokens][16]
+    uint16_t* v_dst;             // [B][h_kv][ceil(cache_tokens/16)][d][16], or pages
+                                 // [num_pages][h_kv][page_tokens/16][d][16]
+    const int32_t* block_table;  // [B][max_pages], or nullptr: contiguous caches
+    int32_t batch, n_new, h_kv, pos0;
+    int32_t cache_tokens;        // capacity of the contiguous caches
+    int32_t zero_tail;           // V: write zeros to the slots of the last block past the source
+    int32_t max_pages, num_pages, page_tokens;
+    uint32_t rope_rho_hi[kMaxPairs];  // used when the keys are turned
     uint32_t rope_rho_lo[kMaxPairs];
 };
 
-struct PackParams {
-    const uint16_t* src;  // [B][n_k][h_kv][d]: tokens pos0 .. pos0 + n_k - 1
-    uint16_t* dst;        // K: [B][h_kv][d/16][cache_tokens][16];
-                          // V: [B][h_kv][ceil(cache_tokens/16)][d][16]
-    int32_t batch, n_k, h_kv;
-    int32_t pos0;          // cache position of the first source token
-    int32_t cache_tokens;  // capacity of dst
-    int32_t zero_tail;     // V: write zeros to the slots of the touched blocks past the source
-};
-
-// One pass of RoPE into a pair-chunk-major K cache (rotate.hip).  Whole cache: key t
-// of every (batch, kv head) at position t, tokens 0 .. n_k - 1, src in the cache layout.
-// Append: src [B][n_k][h_kv][d] (as the projections give it), token t written at cache
-// position pos0 + t and turned to that position.
+// One pass of RoPE over a pair-chunk-major K cache (rotate.hip): key t of every (batch,
+// kv head) turned to position t, tokens 0 .. n_k - 1.
 struct RotateParams {
-    const uint16_t* src;   // [B][h_kv][d/16][cache_tokens][16] (whole) or [B][n_k][h_kv][d] (append)
-    uint16_t* dst;         // [B][h_kv][d/16][cache_tokens][16]; only the tokens named are written
+    const uint16_t* src;   // [B][h_kv][d/16][cache_tokens][16]
+    uint16_t* dst;         // same layout; only the tokens named are written
     int32_t batch, n_k, h_kv, cache_tokens;
-    int32_t pos0;          // append: cache position of the first source token
     uint32_t rope_rho_hi[kMaxPairs];
     uint32_t rope_rho_lo[kMaxPairs];
 };
@@ -125,12 +113,8 @@ struct RotateParams {
 hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_prefill_rotating(const PrefillRotParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_decode(const DecodeParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_pack_kcache(const PackParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_pack_vcache(const PackParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_append_paged(const AppendPagedParams& p, int head_dim, hipStream_t stream);
+hipError_t launch_append(const AppendParams& p, bool turn, int head_dim, hipStream_t stream);
 hipError_t launch_rotate_kcache(const RotateParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_append_rotated_k(const RotateParams& p, int head_dim, hipStream_t stream);
-hipError_t launch_append_paged_rotated(const RotatePagedParams& p, int head_dim, hipStream_t stream);
 
 // Decode split plan of a uniform batch: number of KV splits per (batch, kv head).
 int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k);

@@ -3,7 +3,7 @@
 // the split/merge decomposition is the one Sec. 5 describes), over a
 // pair-chunk-major K cache so that pruned pairs are never read from HBM.
 //
-// Caches (both produced from [B][n_k][h_kv][d] by the pack kernels below):
+// Caches (both produced from [B][n_k][h_kv][d] by the appends of rotate.hip):
 //   K [B][h_kv][d/16][n_k][16]: chunk c of a head is a contiguous stream over
 //     tokens of 16 bf16 = dims [8c, 8c+8) then [d/2 + 8c, d/2 + 8c + 8).  With the
 //     query at position q_pos, token t sits at distance z = q_pos - t, and chunk c
@@ -602,98 +602,6 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const DecodeParams p)
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void pack_kcache_kernel(const PackParams p) {
-    constexpr int kChunks = D / 16;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const int64_t total = int64_t(p.batch) * p.n_k * p.h_kv * kChunks;
-    for (int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x; idx < total;
-         idx += int64_t(gridDim.x) * 256) {
-        const int c = int(idx % kChunks);
-        int64_t r = idx / kChunks;
-        const int g = int(r % p.h_kv);
-        r /= p.h_kv;
-        const int t = int(r % p.n_k);
-        const int b = int(r / p.n_k);
-        const uint16_t* src = p.src + ((int64_t(b) * p.n_k + t) * p.h_kv + g) * D;
-        const u32x4 lo = *reinterpret_cast<const u32x4*>(src + 8 * c);
-        const u32x4 hi = *reinterpret_cast<const u32x4*>(src + D / 2 + 8 * c);
-        uint16_t* dst = p.dst + (((int64_t(b) * p.h_kv + g) * kChunks + c) * p.cache_tokens +
-                                 p.pos0 + t) * 16;
-        *reinterpret_cast<u32x4*>(dst) = lo;
-        *reinterpret_cast<u32x4*>(dst + 8) = hi;
-    }
-}
-
-// V blocks: one thread per (batch, kv head, touched 16-token block, dim); slot
-// 8h + e of the row holds token 8*(e/4) + 4h + e%4 of the block.  Slots of
-// tokens outside pos0 .. pos0 + n_k - 1 keep their contents (or become 0 past the
-// source when zero_tail is set).
-template <int D>
-__global__ __launch_bounds__(256) void pack_vcache_kernel(const PackParams p) {
-    const int blk0 = p.pos0 / 16;
-    const int nblk = (p.pos0 + p.n_k + 15) / 16 - blk0;  // blocks touched
-    const int cache_blk = (p.cache_tokens + 15) / 16;
-    const int64_t total = int64_t(p.batch) * p.h_kv * nblk * D;
-    for (int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x; idx < total;
-         idx += int64_t(gridDim.x) * 256) {
-        const int x = int(idx % D);
-        int64_t r = idx / D;
-        const int blk = blk0 + int(r % nblk);
-        r /= nblk;
-        const int g = int(r % p.h_kv);
-        const int b = int(r / p.h_kv);
-        uint16_t* dst = p.dst + ((int64_t(b) * p.h_kv + g) * cache_blk + blk) * int64_t(D) * 16 +
-                        int64_t(x) * 16;
-#pragma unroll
-        for (int pos = 0; pos < 16; ++pos) {
-            const int h = pos >> 3, e = pos & 7;
-            const int t = 16 * blk + 8 * (e >> 2) + 4 * h + (e & 3) - p.pos0;  // source token
-            if (t >= 0 && t < p.n_k)
-                dst[pos] = p.src[((int64_t(b) * p.n_k + t) * p.h_kv + g) * D + x];
-            else if (t >= p.n_k && p.zero_tail)
-                dst[pos] = uint16_t(0);
-        }
-    }
-}
-
-// Paged append: one thread per (batch, new token, kv head, 8-dim piece); K pieces
-// go to the token's chunk stream in its page, V elements to the slots of the
-// token's 16-token block in its page (slot 8h + e holds token 8(e/4) + 4h + e%4).
-template <int D>
-__global__ __launch_bounds__(256) void append_paged_kernel(const AppendPagedParams p) {
-    constexpr int kChunks = D / 16;
-    constexpr int kPieces = D / 8;  // 8-dim pieces of one (token, head) row
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const int64_t total = int64_t(p.batch) * p.n_new * p.h_kv * kPieces;
-    for (int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x; idx < total;
-         idx += int64_t(gridDim.x) * 256) {
-        const int pc = int(idx % kPieces);
-        int64_t r = idx / kPieces;
-        const int g = int(r % p.h_kv);
-        r /= p.h_kv;
-        const int t = int(r % p.n_new);
-        const int b = int(r / p.n_new);
-        const int pos = p.pos0 + t;
-        const int page = p.block_table[int64_t(b) * p.max_pages + pos / p.page_tokens];
-        if (page < 0 || page >= p.num_pages) continue;
-        const int slot = pos % p.page_tokens;
-        const int64_t src = ((int64_t(b) * p.n_new + t) * p.h_kv + g) * D + 8 * pc;
-        // K: piece pc = dims [8 pc, 8 pc + 8) is half (pc >= kChunks) of chunk pc % kChunks
-        const int c = pc % kChunks, half = pc / kChunks;
-        uint16_t* kd = p.k_pages + (((int64_t(page) * p.h_kv + g) * kChunks + c) * p.page_tokens +
-                                    slot) * 16 + 8 * half;
-        *reinterpret_cast<u32x4*>(kd) = *reinterpret_cast<const u32x4*>(p.k_src + src);
-        // V: dims 8 pc .. 8 pc + 7 of this token, one slot each
-        const int e16 = slot % 16;  // token within its 16-token block
-        const int h = (e16 % 8) / 4, e = (e16 / 8) * 4 + e16 % 4;  // slot 8h + e
-        uint16_t* vd = p.v_pages + ((int64_t(page) * p.h_kv + g) * (p.page_tokens / 16) + slot / 16) *
-                                       int64_t(D) * 16 + 8 * h + e;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) vd[int64_t(8 * pc + x) * 16] = p.v_src[src + x];
-    }
-}
-
-template <int D>
 hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     // ragged: one workgroup per possible work item (at most p.splits + batch)
     const bool ragged = p.n_k_rows != nullptr;
@@ -708,11 +616,6 @@ hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     hipLaunchKernelGGL(decode_merge_kernel<D>, dim3(unsigned(p.batch * p.h_q), unsigned(D / 32)),
                        dim3(256), 0, stream, p);
     return hipGetLastError();
-}
-
-unsigned pack_blocks(int64_t total) {
-    int64_t blocks = (total + 255) / 256;
-    return unsigned(blocks > 65536 ? 65536 : blocks);
 }
 
 }  // namespace
@@ -762,37 +665,6 @@ hipError_t noalloc_scratch(void** out) {
     }
     *out = g_scratch_addr[dev];
     return hipSuccess;
-}
-
-hipError_t launch_pack_kcache(const PackParams& p, int head_dim, hipStream_t stream) {
-    const int64_t total = int64_t(p.batch) * p.n_k * p.h_kv * (head_dim / 16);
-    (void)hipGetLastError();
-    if (head_dim == 64)
-        hipLaunchKernelGGL(pack_kcache_kernel<64>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(pack_kcache_kernel<128>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_append_paged(const AppendPagedParams& p, int head_dim, hipStream_t stream) {
-    const int64_t total = int64_t(p.batch) * p.n_new * p.h_kv * (head_dim / 8);
-    (void)hipGetLastError();
-    if (head_dim == 64)
-        hipLaunchKernelGGL(append_paged_kernel<64>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(append_paged_kernel<128>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_vcache(const PackParams& p, int head_dim, hipStream_t stream) {
-    const int64_t total = int64_t(p.batch) * p.h_kv *
-                          ((p.pos0 + p.n_k + 15) / 16 - p.pos0 / 16) * head_dim;
-    (void)hipGetLastError();
-    if (head_dim == 64)
-        hipLaunchKernelGGL(pack_vcache_kernel<64>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(pack_vcache_kernel<128>, dim3(pack_blocks(total)), dim3(256), 0, stream, p);
-    return hipGetLastError();
 }
 
 }  // namespace atf

@@ -1,24 +1,24 @@
-// RoPE at write time (App. B sets it against rotating at read time): the keys of an
-// unrotated K cache turned once, each to its own position, into a second cache or in
-// place, and the same rotation fused into the cache append; the pre-rotated prefill and
-// decode then read the result.  It costs one read and one write of the keys and every
-// (key, pair) rotation, whatever the window keeps, and a rotated copy's memory; a long
-// prefill over an unrotated cache can take it instead of the read-time path when that
-// memory is at hand.
+// Writes into the caches: the appends and packs (keys as given or turned to their
+// positions on the way in, contiguous or paged caches), and RoPE over a whole unrotated K
+// cache in one pass.  Rotation at write time (App. B sets it against rotating at read
+// time) costs one read and one write of the keys and every (key, pair) rotation, whatever
+// the window keeps; a long prefill over an unrotated cache can take it instead of the
+// read-time path when the rotated copy's memory is at hand.
 //
-// Memory-bound.  One thread per (key, pair-chunk): the chunk's 32 bytes (the first
-// components of its 8 pairs, then the second) are read as two 16-byte loads, the 8
-// angles evaluated directly (0.64 fixed-point fraction, v_cos_f32 / v_sin_f32 in
-// revolutions), rotated in fp32 and rounded to bf16.  Whole cache: grid y = the
-// (batch, kv head, chunk) stream, x over its tokens, so a block's chunk and its 8
-// frequencies are uniform and consecutive threads touch consecutive 32-byte records.
-
+// All memory-bound.  Angles are evaluated directly (0.64 fixed-point fraction, v_cos_f32 /
+// v_sin_f32 in revolutions), rotated in fp32 and rounded to bf16.
 #include "atf_internal.hpp"
 #include "rope.hpp"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace atf {
 namespace {
 
+// Whole cache: one thread per (key, pair-chunk) record; grid y = the (batch, kv head,
+// chunk) stream, x over its tokens, so a block's chunk and its 8 frequencies are uniform
+// and consecutive threads touch consecutive 32-byte records.
 template <int D>
 __global__ __launch_bounds__(256) void rotate_kcache_kernel(const RotateParams p) {
     constexpr int kChunks = D / 16;
@@ -44,114 +44,177 @@ __global__ __launch_bounds__(256) void rotate_kcache_kernel(const RotateParams p
     }
 }
 
-// Append with RoPE: keys as the projections give them ([B][n_k][h_kv][d], unrotated),
-// each turned to its cache position pos0 + t and written into the pair-chunk-major
-// cache, one thread per (token, kv head, chunk) as atf_pack_kcache lays them out.
-template <int D>
-__global__ __launch_bounds__(256) void append_rotated_k_kernel(const RotateParams p) {
+// Append: K and V of the new tokens in one launch.  One wave per unit = (batch, 16-token
+// block of cache positions, kv head), heads fastest, so that the waves of a workgroup read
+// neighbouring rows of the source ([B][n_new][h_kv][d]).
+//   K: one (token, chunk) record per lane and step: 16 bytes of each half of the chunk's
+//      pairs in, 32 contiguous bytes of the chunk's stream out; 16 tokens of a chunk are 512
+//      contiguous bytes.
+//   V: a lane takes 2 dims x the 8 tokens of one half of the block's slots (slot 8h + e
+//      holds token 8(e/4) + 4h + e%4): eight 4-byte loads, 256 (d = 64: 128) contiguous
+//      bytes per token, transposed in registers into two 16-byte stores.  A block that the
+//      call does not cover whole is written slot by slot, so the other slots keep their
+//      contents (or become zero past the source when zero_tail is set).
+// Bound by HBM; every load of a unit is in flight before the first store.  One thread per
+// (token, chunk) and per (block, dim) with a 64-bit division chain each and 2-byte stores
+// of V, in two launches, took 96 us for 16,384 tokens of 8 heads at d = 128 (134 MB moved,
+// rotated); this takes 33.7 us (4.0 TB/s).
+enum { kKeysNone = 0, kKeysAsGiven = 1, kKeysTurned = 2 };
+
+template <int D, int kKeys, bool kValues, bool kPaged>
+__global__ __launch_bounds__(256) void append_kernel(const AppendParams p) {
     constexpr int kChunks = D / 16;
-    const int64_t total = int64_t(p.batch) * p.n_k * p.h_kv * kChunks;
-    for (int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x; idx < total;
-         idx += int64_t(gridDim.x) * 256) {
-        const int c = int(idx % kChunks);
-        int64_t r = idx / kChunks;
-        const int g = int(r % p.h_kv);
-        r /= p.h_kv;
-        const int t = int(r % p.n_k);
-        const int b = int(r / p.n_k);
-        const uint16_t* src = p.src + ((int64_t(b) * p.n_k + t) * p.h_kv + g) * D;
-        const rope::u32x4_t x = *reinterpret_cast<const rope::u32x4_t*>(src + 8 * c);
-        const rope::u32x4_t y = *reinterpret_cast<const rope::u32x4_t*>(src + D / 2 + 8 * c);
-        const uint32_t pos = uint32_t(p.pos0 + t);
-        float cs8[8], sn8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float u = rope::revolutions(pos, make_uint2(p.rope_rho_hi[8 * c + e],
-                                                              p.rope_rho_lo[8 * c + e]));
-            cs8[e] = __builtin_amdgcn_cosf(u);
-            sn8[e] = __builtin_amdgcn_sinf(u);
+    constexpr int kSteps = D / 64;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63;
+    const int blk0 = p.pos0 / 16;
+    const int nblk = (p.pos0 + p.n_new - 1) / 16 + 1 - blk0;  // blocks touched
+    const uint32_t units = uint32_t(p.batch) * uint32_t(nblk) * uint32_t(p.h_kv);
+    for (uint32_t unit = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); unit < units;
+         unit += gridDim.x * 4) {
+        const int g = int(unit % uint32_t(p.h_kv));
+        const uint32_t rest = unit / uint32_t(p.h_kv);
+        const int blk = blk0 + int(rest % uint32_t(nblk));
+        const int b = int(rest / uint32_t(nblk));
+        // first token of the block in the source, and the tokens of the block in it
+        const int t0 = 16 * blk - p.pos0;
+        const int lo = max(0, -t0), hi = min(16, p.n_new - t0);
+        // the unit's place in the caches: chunk c of block token t at
+        // kd + (c * kstride + t) * 16, dim x at vd + x * 16
+        int64_t kd, kstride, vd;
+        if constexpr (kPaged) {
+            const int page = p.block_table[int64_t(b) * p.max_pages + 16 * blk / p.page_tokens];
+            if (page < 0 || page >= p.num_pages) continue;
+            const int at = 16 * blk % p.page_tokens;  // a page holds whole blocks
+            const int64_t ph = int64_t(page) * p.h_kv + g;
+            kd = (ph * kChunks * p.page_tokens + at) * 16;
+            kstride = p.page_tokens;
+            vd = (ph * (p.page_tokens / 16) + at / 16) * int64_t(D) * 16;
+        } else {
+            const int64_t bh = int64_t(b) * p.h_kv + g;
+            kd = (bh * kChunks * p.cache_tokens + 16 * int64_t(blk)) * 16;
+            kstride = p.cache_tokens;
+            vd = (bh * ((int64_t(p.cache_tokens) + 15) / 16) + blk) * int64_t(D) * 16;
         }
-        uint16_t* dst = p.dst + (((int64_t(b) * p.h_kv + g) * kChunks + c) * p.cache_tokens + pos) * 16;
-        *reinterpret_cast<rope::u32x4_t*>(dst) = rope::rotate_cs(x, y, 0, cs8, sn8);
-        *reinterpret_cast<rope::u32x4_t*>(dst + 8) = rope::rotate_cs(y, x, 1, cs8, sn8);
+        // element offset of (block token t, dim 0) in the sources: src0 + t * row
+        const int64_t row = int64_t(p.h_kv) * D;
+        const int64_t src0 = ((int64_t(b) * p.n_new + t0) * p.h_kv + g) * D;
+
+        // W: the call covers the whole block (no test per token)
+        auto move = [&](auto whole_tag) __attribute__((always_inline)) {
+            constexpr bool W = decltype(whole_tag)::value;
+            u32x4 kx[kSteps], ky[kSteps];
+            [[maybe_unused]] uint32_t vx[kSteps][8];
+            if constexpr (kKeys != kKeysNone) {
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j) {
+                    const int t = lane & 15, c = (lane >> 4) + 4 * j;
+                    kx[j] = ky[j] = u32x4{0u, 0u, 0u, 0u};
+                    if (W || (t >= lo && t < hi)) {
+                        const uint16_t* src = p.k_src + src0 + t * row + 8 * c;
+                        kx[j] = *reinterpret_cast<const u32x4*>(src);
+                        ky[j] = *reinterpret_cast<const u32x4*>(src + D / 2);
+                    }
+                }
+            }
+            if constexpr (kValues && W) {
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j) {
+                    const int it = lane + 64 * j, dp = it % (D / 2), h = it / (D / 2);
+                    const uint16_t* src = p.v_src + src0 + 4 * h * row + 2 * dp;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        vx[j][e] = *reinterpret_cast<const uint32_t*>(src + (8 * (e / 4) + e % 4) * row);
+                }
+            }
+            if constexpr (kKeys != kKeysNone) {
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j) {
+                    const int t = lane & 15, c = (lane >> 4) + 4 * j;
+                    if constexpr (kKeys == kKeysTurned) {
+                        float cs8[8], sn8[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const float u = rope::revolutions(uint32_t(16 * blk + t),
+                                                              make_uint2(p.rope_rho_hi[8 * c + e], p.rope_rho_lo[8 * c + e]));
+                            cs8[e] = __builtin_amdgcn_cosf(u);
+                            sn8[e] = __builtin_amdgcn_sinf(u);
+                        }
+                        const u32x4 x = kx[j], y = ky[j];
+                        kx[j] = rope::rotate_cs(x, y, 0, cs8, sn8);
+                        ky[j] = rope::rotate_cs(y, x, 1, cs8, sn8);
+                    }
+                    if (W || (t >= lo && t < hi)) {
+                        uint16_t* dst = p.k_dst + kd + (c * kstride + t) * 16;
+                        *reinterpret_cast<u32x4*>(dst) = kx[j];
+                        *reinterpret_cast<u32x4*>(dst + 8) = ky[j];
+                    }
+                }
+            }
+            if constexpr (kValues && W) {
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j) {
+                    const int it = lane + 64 * j, dp = it % (D / 2), h = it / (D / 2);
+                    uint16_t* dst = p.v_dst + vd + 32 * dp + 8 * h;  // slots of dims 2 dp, 2 dp + 1
+                    u32x4 even, odd;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        even[q] = __builtin_amdgcn_perm(vx[j][2 * q + 1], vx[j][2 * q], 0x05040100u);
+                        odd[q] = __builtin_amdgcn_perm(vx[j][2 * q + 1], vx[j][2 * q], 0x07060302u);
+                    }
+                    *reinterpret_cast<u32x4*>(dst) = even;
+                    *reinterpret_cast<u32x4*>(dst + 16) = odd;
+                }
+            }
+            if constexpr (kValues && !W) {
+                const int end = p.zero_tail ? 16 : hi;
+                if (lane < D / 2) {
+#pragma unroll 4
+                    for (int t = lo; t < end; ++t) {
+                        const int slot = 8 * (t % 8 / 4) + 4 * (t / 8) + t % 4;
+                        uint32_t x = 0u;
+                        if (t < hi) x = *reinterpret_cast<const uint32_t*>(p.v_src + src0 + t * row + 2 * lane);
+                        uint16_t* dst = p.v_dst + vd + 32 * lane + slot;
+                        dst[0] = uint16_t(x);
+                        dst[16] = uint16_t(x >> 16);
+                    }
+                }
+            }
+        };
+        if (hi - lo == 16)
+            move(std::true_type{});
+        else
+            move(std::false_type{});
     }
 }
 
-// The paged form: one thread per (token, kv head, chunk), the token's page from the
-// row's block table (entries outside the pool are skipped); K rotated as above into the
-// page's pair-chunk-major slot, and the two 8-dim pieces of V that share the chunk's
-// dims (d0 = 8 c and d/2 + 8 c) copied into the page's 16-token block, slot 8 h + e for
-// token 8 (e / 4) + 4 h + e % 4 of the block, as atf_cache_append_paged writes them.
+template <int D, int kKeys, bool kValues, bool kPaged>
+hipError_t launch_append_k(const AppendParams& p, hipStream_t stream) {
+    const int64_t nblk = (p.pos0 + p.n_new - 1) / 16 + 1 - p.pos0 / 16;
+    const int64_t units = int64_t(p.batch) * nblk * p.h_kv;
+    // (16 rows of 128 bytes or more each: 2^31 units do not fit the memory)
+    if (units < 1 || units > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const int64_t blocks = std::min<int64_t>((units + 3) / 4, 1 << 20);
+    (void)hipGetLastError();
+    hipLaunchKernelGGL((append_kernel<D, kKeys, kValues, kPaged>), dim3(unsigned(blocks)), dim3(256), 0, stream, p);
+    return hipGetLastError();
+}
+
 template <int D>
-__global__ __launch_bounds__(256) void append_paged_rotated_kernel(const RotatePagedParams rp) {
-    constexpr int kChunks = D / 16;
-    const AppendPagedParams& p = rp.a;
-    const int64_t total = int64_t(p.batch) * p.n_new * p.h_kv * kChunks;
-    for (int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x; idx < total;
-         idx += int64_t(gridDim.x) * 256) {
-        const int c = int(idx % kChunks);
-        int64_t r = idx / kChunks;
-        const int g = int(r % p.h_kv);
-        r /= p.h_kv;
-        const int t = int(r % p.n_new);
-        const int b = int(r / p.n_new);
-        const int pos = p.pos0 + t;
-        const int page = p.block_table[int64_t(b) * p.max_pages + pos / p.page_tokens];
-        if (page < 0 || page >= p.num_pages) continue;
-        const int slot = pos % p.page_tokens;
-        const int64_t src = ((int64_t(b) * p.n_new + t) * p.h_kv + g) * D;
-        const rope::u32x4_t x = *reinterpret_cast<const rope::u32x4_t*>(p.k_src + src + 8 * c);
-        const rope::u32x4_t y = *reinterpret_cast<const rope::u32x4_t*>(p.k_src + src + D / 2 + 8 * c);
-        float cs8[8], sn8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float u = rope::revolutions(uint32_t(pos), make_uint2(rp.rope_rho_hi[8 * c + e],
-                                                                        rp.rope_rho_lo[8 * c + e]));
-            cs8[e] = __builtin_amdgcn_cosf(u);
-            sn8[e] = __builtin_amdgcn_sinf(u);
-        }
-        uint16_t* kd = p.k_pages + (((int64_t(page) * p.h_kv + g) * kChunks + c) * p.page_tokens + slot) * 16;
-        *reinterpret_cast<rope::u32x4_t*>(kd) = rope::rotate_cs(x, y, 0, cs8, sn8);
-        *reinterpret_cast<rope::u32x4_t*>(kd + 8) = rope::rotate_cs(y, x, 1, cs8, sn8);
-        const int e16 = slot % 16;
-        const int h = (e16 % 8) / 4, e = (e16 / 8) * 4 + e16 % 4;
-        uint16_t* vd = p.v_pages + ((int64_t(page) * p.h_kv + g) * (p.page_tokens / 16) + slot / 16) *
-                                       int64_t(D) * 16 + 8 * h + e;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int d0 = 8 * c + half * (D / 2);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) vd[int64_t(d0 + q) * 16] = p.v_src[src + d0 + q];
-        }
-    }
+hipError_t launch_append_d(const AppendParams& p, bool turn, hipStream_t stream) {
+    if (p.block_table != nullptr)
+        return turn ? launch_append_k<D, kKeysTurned, true, true>(p, stream)
+                    : launch_append_k<D, kKeysAsGiven, true, true>(p, stream);
+    if (p.v_src == nullptr) return launch_append_k<D, kKeysAsGiven, false, false>(p, stream);
+    if (p.k_src == nullptr) return launch_append_k<D, kKeysNone, true, false>(p, stream);
+    return turn ? launch_append_k<D, kKeysTurned, true, false>(p, stream)
+                : launch_append_k<D, kKeysAsGiven, true, false>(p, stream);
 }
 
 }  // namespace
 
-hipError_t launch_append_paged_rotated(const RotatePagedParams& p, int head_dim, hipStream_t stream) {
-    const int64_t total = int64_t(p.a.batch) * p.a.n_new * p.a.h_kv * (head_dim / 16);
-    if (total < 1) return hipErrorInvalidConfiguration;
-    const int64_t blocks = (total + 255) / 256;
-    const unsigned grid = unsigned(blocks < 16384 ? blocks : 16384);
-    (void)hipGetLastError();
-    if (head_dim == 64)
-        hipLaunchKernelGGL(append_paged_rotated_kernel<64>, dim3(grid), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(append_paged_rotated_kernel<128>, dim3(grid), dim3(256), 0, stream, p);
-    return hipGetLastError();
-}
-
-hipError_t launch_append_rotated_k(const RotateParams& p, int head_dim, hipStream_t stream) {
-    const int64_t total = int64_t(p.batch) * p.n_k * p.h_kv * (head_dim / 16);
-    if (total < 1) return hipErrorInvalidConfiguration;
-    const int64_t blocks = (total + 255) / 256;
-    const unsigned grid = unsigned(blocks < 16384 ? blocks : 16384);
-    (void)hipGetLastError();
-    if (head_dim == 64)
-        hipLaunchKernelGGL(append_rotated_k_kernel<64>, dim3(grid), dim3(256), 0, stream, p);
-    else
-        hipLaunchKernelGGL(append_rotated_k_kernel<128>, dim3(grid), dim3(256), 0, stream, p);
-    return hipGetLastError();
+hipError_t launch_append(const AppendParams& p, bool turn, int head_dim, hipStream_t stream) {
+    return head_dim == 64 ? launch_append_d<64>(p, turn, stream) : launch_append_d<128>(p, turn, stream);
 }
 
 hipError_t launch_rotate_kcache(const RotateParams& p, int head_dim, hipStream_t stream) {

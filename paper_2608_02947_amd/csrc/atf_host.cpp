@@ -2,6 +2,7 @@
 // retained-term count, and dispatch to the gfx950 kernels.  See include/atf.h.
 #include "atf.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <new>
@@ -168,8 +169,6 @@ u128 pair_count(int64_t W, int64_t p0, int64_t p1, int64_t n_k) {
 namespace atf {
 
 int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k) {
-    // enough workgroups to fill 256 CUs several times over, but never a split
-    // shorter than one workgroup step
     const int64_t target_groups = 1024;
     int64_t s = (target_groups + int64_t(batch) * h_kv - 1) / (int64_t(batch) * h_kv);
     const int64_t max_s = (n_k + kDecodeTokenStep - 1) / kDecodeTokenStep;
@@ -180,15 +179,45 @@ int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k) {
 }
 
 int32_t decode_ragged_items(int32_t cols) {
-    // the batch's keys are cut into about this many equal spans per column, whatever
-    // the row lengths (measured on batches of 8 rows at d = 128 with 8 KV heads:
-    // 2048 workgroups beat 1024 by 5-12 % and 4096 by 0-20 %, on rows of 4K-128K keys,
-    // of 128K keys, and of one 128K row beside seven 1K rows)
     const int64_t target_groups = 2048;
     int64_t s = (target_groups + cols - 1) / cols;
     if (s > kDecodeMaxSplits - 1) s = kDecodeMaxSplits - 1;
     if (s < 1) s = 1;
     return static_cast<int32_t>(s);
+}
+
+// Splits a uniform batch uses, at most the decode_splits() its workspace has room for.
+//
+// Up to 16 heads per workgroup: as many workgroups as the CUs hold at once, 3 of
+// decode_split16_kernel (768) or 2 where it rotates keys (512, at d = 128; its tables are
+// made anew by every workgroup), so that the batch runs in one round of equal splits:
+// 2^20 keys, 28/4 heads 283 us with 1024, 273 with 768; batch 8 at 32,768 keys, 24/8 heads
+// 156 -> 153; rotating, batch 2 at 100,003 keys 65.9 -> 63.5, batch 8 at 8,200 36.1 -> 30.7
+// (512; 31.6 with 768).  More heads: 1024, two rounds of the 2 workgroups per CU of
+// decode_split_kernel (2048 is 6 % slower at 2^20 keys).  The steps are then spread evenly:
+// 65 steps over 12 splits are 11 splits of 6, not 10 of 6 and one of 5 beside an empty one.
+int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
+                           int32_t heads_per_block, bool rotate) {
+    const int64_t room = decode_splits(batch, h_kv, n_k);
+    const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
+    const int64_t target = heads_per_block > 16 ? 1024 : rotate ? 512 : 768;
+    const int64_t steps = (n_valid + kDecodeTokenStep - 1) / kDecodeTokenStep;
+    int64_t s = heads_per_block > 16 ? room : std::min(room, std::max<int64_t>(1, target / cols));
+    s = std::max<int64_t>(1, std::min(s, steps));
+    const int64_t per = (steps + s - 1) / s;
+    return static_cast<int32_t>(std::max<int64_t>(1, (steps + per - 1) / per));
+}
+
+// Work items the keys of a ragged batch are spread over, at most the decode_ragged_items()
+// its workspace has room for.  1536 workgroups, two rounds of decode_split16_kernel's 768
+// (rows differ, so one round leaves the CUs of the short ones idle: 768 takes 1.08 times as
+// long on 8 rows of 6K to 120K keys of 24/8 heads), against 2048: 8 rows up to 120K keys
+// 219 -> 214 us (24/8 heads), 124 -> 120 (28/4); 4 rows up to 60K 65 -> 63, 38 -> 36; 24
+// rows up to 30K 159 -> 161, 94 -> 92.  decode_split_kernel keeps 2048 (5-12 % faster than
+// 1024, up to 20 % than 4096).
+int32_t decode_plan_items(int32_t cols, int32_t heads_per_block) {
+    const int32_t room = decode_ragged_items(cols);
+    return heads_per_block > 16 ? room : std::min(room, std::max(1, 1536 / cols));
 }
 
 }  // namespace atf
@@ -698,17 +727,22 @@ int decode_impl(const char* fn, const void* q, const void* k_cache, const void* 
         // keys in about `splits` equal spans (multiples of the workgroup's token step)
         // per column, each row cut into whole spans of its own keys
         p.n_valid = static_cast<int32_t>(n_k);
-        p.splits = atf::decode_ragged_items(h_kv * (group / hpb));
+        p.splits = atf::decode_plan_items(h_kv * (group / hpb), hpb);
         p.split_tokens = 0;
     } else {
         const int64_t last = q_pos < n_k - 1 ? q_pos : n_k - 1;
         p.n_valid = static_cast<int32_t>(last + 1);
-        const int32_t splits = atf::decode_splits(batch, h_kv, n_k);
+        const int32_t splits =
+            atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, rope.rotate);
         p.splits = splits;
-        const int64_t per = (p.n_valid + splits - 1) / splits;
-        const int64_t step_tokens = (per + atf::kDecodeTokenStep - 1) / atf::kDecodeTokenStep *
-                                    atf::kDecodeTokenStep;
-        if (step_tokens * splits >= kPosLimit)
+        const auto step_of = [&](int64_t s) {
+            const int64_t per = (p.n_valid + s - 1) / s;
+            return (per + atf::kDecodeTokenStep - 1) / atf::kDecodeTokenStep * atf::kDecodeTokenStep;
+        };
+        const int64_t step_tokens = step_of(splits);
+        // (the longest plan is what a call is refused by, whichever it uses)
+        const int64_t room = atf::decode_splits(batch, h_kv, n_k);
+        if (step_of(room) * room >= kPosLimit || step_tokens * splits >= kPosLimit)
             return fail(ATF_EINVAL, "%s: cache too long for the split plan", fn);
         p.split_tokens = static_cast<int32_t>(step_tokens);
     }

@@ -116,10 +116,14 @@ hipError_t launch_decode(const DecodeParams& p, int head_dim, hipStream_t stream
 hipError_t launch_append(const AppendParams& p, bool turn, int head_dim, hipStream_t stream);
 hipError_t launch_rotate_kcache(const RotateParams& p, int head_dim, hipStream_t stream);
 
-// Decode split plan of a uniform batch: number of KV splits per (batch, kv head).
+// Most splits per (batch, kv head) of a uniform batch, and most work items per column of
+// `cols` = kv heads x head subgroups of a ragged one: what the workspace has room for.
 int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k);
-// Work items of a ragged batch (per column of `cols` = kv heads x head subgroups).
 int32_t decode_ragged_items(int32_t cols);
+// The numbers a call uses.
+int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
+                           int32_t heads_per_block, bool rotate);
+int32_t decode_plan_items(int32_t cols, int32_t heads_per_block);
 // Tokens handled per decode workgroup iteration (the split granularity).
 constexpr int32_t kDecodeTokenStep = 128;
 // Largest split count the merge kernel accepts.

@@ -47,6 +47,7 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
@@ -55,6 +56,20 @@ constexpr float kRescale = 8.0f;  // lazy-rescale threshold, log2 units
 __device__ __forceinline__ f32x16_t mfma(u32x4_t a, u32x4_t b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                    __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4_t mfma16(u32x4_t a, u32x4_t b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
+                                                   __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+// 16 bytes per lane at base + off (base wave-uniform), or zeros, nothing read, in a lane
+// whose off is kOutOfRange
+constexpr uint32_t kOutOfRange = 0xFFFFFFFFu;
+__device__ __forceinline__ u32x4_t buffer_load_b128(const char* base, uint32_t off) {
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, int(0xFFFFFFF0u), 0x00020000);
+    return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, int(off), 0, 0));
 }
 
 __device__ __forceinline__ f32x16_t zero16() {
@@ -528,6 +543,325 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_split_kernel(const Deco
     }
 }
 
+// ---- Up to 16 query heads per KV head: the same work on 16x16x32 matrix instructions.
+//
+// decode_split_kernel gives the heads 32 matrix columns.  With 16 or fewer, half of its
+// accumulators, scores and exponentials are columns nobody reads, and its 215 registers
+// leave a CU 8 waves.  Here the heads are the columns of v_mfma_f32_16x16x32_bf16 tiles:
+//   S^T[token][head]: 16 tokens x 32 dims (two pair-chunks) per product; lane l holds head
+//     l % 16 and, with g = l / 16, the tokens 16 (g / 2) + 8 s + 4 (g % 2) + v (v < 4) of
+//     product s = 0, 1 of a 32-token block: the tokens of one 16-byte V piece
+//   O^T[d][head]: 16 dims x 32 tokens per product, A = V^T straight from the packed blocks
+//     (lane: dim l % 16, slots 8 (g % 2) .. + 7 of 16-token block g / 2), B = the scores'
+//     registers rounded to bf16 as they are
+// A K operand is 16 bytes per lane: chunk 2 m + g / 2, half g % 2.  All loads are buffer
+// loads whose lanes go out of range where nothing is wanted (a chunk no token keeps, a
+// token past the split's end, a V block past the row's keys): no bytes move, zeros arrive,
+// and every block issues the same number of loads.
+//
+// 166 registers at d = 128 (3 waves per SIMD; 223, 2 waves, where keys are rotated) and
+// 116 at d = 64 (4; 160, 3).  HBM bounds the long caches; the short ones gain from the
+// shorter block and the waves in flight.  decode_split_kernel -> this one, us: batch 8 at
+// 8,200 keys, 24/8 heads 50.3 -> 41.6; 32,768 keys, 28/4 24.7 -> 17.6; 131,072 keys,
+// 16/16 heads of d = 64 90.3 -> 68.8; batch 40 up to 5,000 keys, 28/4, paged 43.4 -> 32.2;
+// 2^20 keys, 28/4 283.7 -> 273.3; rotating, batch 2 at 100,003 keys 77.9 -> 63.5.
+template <int D, bool kRot>
+__global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128 ? 3 : 4))) void decode_split16_kernel(const DecodeParams p) {
+    constexpr int kChunks = D / 16;
+    constexpr int kHalf = D / 2;
+    constexpr int kM = D / 32;   // chunk pairs: K operands per 16 tokens
+    constexpr int kDB = D / 16;  // 16-dim blocks of the output
+    constexpr int kOStride = D + 4;
+    constexpr int kCStride = D + 4;
+    __shared__ float red_m[kWaves][16];
+    __shared__ float red_l[kWaves][16];
+    // while the waves stream: the queries, then (rotation) the (cos, sin) of t * theta_r for
+    // the 32 tokens of a block and per wave those of the block's first position; afterwards
+    // the waves' outputs [wave][head][D + 4]
+    constexpr int kTables = 8 * D + (kRot ? 32 * kCStride + kWaves * D : 0);
+    constexpr int kMerge = kWaves * 16 * kOStride;
+    __shared__ __attribute__((aligned(16))) float shared[kTables > kMerge ? kTables : kMerge];
+    float* const s_colcs = shared + 8 * D;
+    float* const s_blkcs = s_colcs + 32 * kCStride;
+    float* const red_o = shared;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15;
+    const int g4 = lane >> 4;
+    const int hf = g4 & 1;   // half of the pairs (K, Q), half of the slots (V)
+    const int up = g4 >> 1;  // chunk of the pair (K, Q), 16-token block (V)
+    const int split = blockIdx.x;
+    const int NH = p.heads_per_block;
+    const int subgroups = p.group / NH;
+    const int g = blockIdx.y / subgroups;
+    const int sub = blockIdx.y % subgroups;
+    const int hq0 = g * p.group + sub * NH;
+    const bool head_ok = r16 < NH;
+
+    int b, n_k = p.n_k, q_pos = p.q_pos, n_valid = p.n_valid, t_begin, t_end;
+    int64_t slot0;
+    if (p.n_k_rows != nullptr) {
+        int64_t span;
+        int32_t* plan = (blockIdx.x == 0 && blockIdx.y == 0 && wave == 0) ? p.ws_plan : nullptr;
+        b = ragged_item(p, split, t_begin, span, plan);
+        if (b < 0) return;
+        n_k = min(max(p.n_k_rows[b], 0), p.n_k);
+        q_pos = min(max(p.q_pos_rows[b], 0), 0x7FFFFFFD);
+        n_valid = min(n_k, q_pos + 1);
+        t_end = int(min(int64_t(n_valid), int64_t(t_begin) + span));
+        slot0 = int64_t(split) * p.h_q + hq0;
+    } else {
+        b = blockIdx.z;
+        t_begin = split * p.split_tokens;
+        t_end = min(n_valid, t_begin + p.split_tokens);
+        slot0 = (int64_t(b) * p.h_q + hq0) * p.splits + split;
+    }
+    b = __builtin_amdgcn_readfirstlane(b);
+    n_k = __builtin_amdgcn_readfirstlane(n_k);
+    q_pos = __builtin_amdgcn_readfirstlane(q_pos);
+    t_begin = __builtin_amdgcn_readfirstlane(t_begin);
+    t_end = __builtin_amdgcn_readfirstlane(t_end);
+    const int64_t cap = p.cache_tokens;
+    const uint16_t* kstream = p.kpcm + (int64_t(b) * p.h_kv + g) * kChunks * cap * 16;
+    const uint16_t* vblocks = p.vpk + (int64_t(b) * p.h_kv + g) * ((cap + 15) / 16) * D * 16;
+    const int my_w = lane < kHalf ? p.win.W[lane] : -1;
+
+    // queries: operand m of lane l at 1024 m + 16 l (each wave writes whole operands)
+    uint2 my_rho = make_uint2(0u, 0u);
+    {
+        const uint16_t* qvec = p.q + (int64_t(b) * p.h_q + hq0 + (head_ok ? r16 : 0)) * D + hf * kHalf;
+        for (int m = wave; m < kM; m += kWaves) {
+            u32x4_t z = {0u, 0u, 0u, 0u};
+            if (head_ok) z = *reinterpret_cast<const u32x4_t*>(qvec + 8 * (2 * m + up));
+            if constexpr (kRot)
+                z = rope::rotate(z, rope::other_half16(z, hf), hf, uint32_t(q_pos),
+                                 &p.rope_rho_hi[8 * (2 * m + up)], &p.rope_rho_lo[8 * (2 * m + up)]);
+            *reinterpret_cast<u32x4_t*>(&shared[256 * m + 4 * lane]) = z;
+        }
+        if constexpr (kRot) {
+            for (int e = tid; e < 32 * kHalf; e += kWaves * 64) {
+                const int cc = e / kHalf, r = e % kHalf;
+                const float u = rope::revolutions(uint32_t(cc), make_uint2(p.rope_rho_hi[r], p.rope_rho_lo[r]));
+                s_colcs[cc * kCStride + 2 * r] = __builtin_amdgcn_cosf(u);
+                s_colcs[cc * kCStride + 2 * r + 1] = __builtin_amdgcn_sinf(u);
+            }
+            if (lane < kHalf) my_rho = make_uint2(p.rope_rho_hi[lane], p.rope_rho_lo[lane]);
+        }
+        __syncthreads();
+    }
+    auto q_frag = [&](int m) __attribute__((always_inline)) {
+        return *reinterpret_cast<const u32x4_t*>(&shared[256 * m + 4 * lane]);
+    };
+
+    f32x4_t oacc[kDB];
+#pragma unroll
+    for (int i = 0; i < kDB; ++i) oacc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, m_thr = -INFINITY, m_neg = 0.f, l_run = 0.f;
+    const float sc = p.scale_log2;
+    uint64_t q_full = 0;
+    u32x4_t qm[kM];  // queries with the pairs outside q_full zeroed
+#pragma unroll
+    for (int m = 0; m < kM; ++m) qm[m] = u32x4_t{0u, 0u, 0u, 0u};
+
+    // this lane's token of K operand s within the block (s adds 8)
+    const int tk0 = 16 * (r16 >> 3) + 4 * ((r16 >> 2) & 1) + (r16 & 3);
+    const uint32_t v_off = uint32_t(r16 * 32 + hf * 16);
+
+    for (int t0 = t_begin + 32 * wave; t0 < t_end; t0 += 32 * kWaves) {
+        const uint16_t* kb = kstream;
+        const uint16_t* vb = vblocks;
+        int64_t kstride = cap;
+        int tb = 0;
+        if (p.block_table != nullptr) {
+            const int pt = p.page_tokens;
+            const int page = min(max(p.block_table[int64_t(b) * p.max_pages + t0 / pt], 0), p.num_pages - 1);
+            kb = p.kpcm + (int64_t(page) * p.h_kv + g) * kChunks * int64_t(pt) * 16;
+            vb = p.vpk + (int64_t(page) * p.h_kv + g) * (pt / 16) * int64_t(D) * 16;
+            kstride = pt;
+            tb = t0 - t0 % pt;
+        }
+        const uint64_t full = __ballot(my_w >= q_pos - t0);
+        const uint64_t keep = __ballot(my_w >= max(0, q_pos - min(t0 + 31, t_end - 1)));
+        // K operands
+        u32x4_t kf[2][kM];
+        const uint32_t k_lane = uint32_t(up) * uint32_t(kstride) * 32u + uint32_t(tk0 * 32 + hf * 16);
+#pragma unroll
+        for (int m = 0; m < kM; ++m) {
+            const char* base = reinterpret_cast<const char*>(kb + (2 * m * kstride + t0 - tb) * 16);
+            const bool even = ((keep >> (16 * m)) & 0xFFull) != 0, odd = ((keep >> (16 * m + 8)) & 0xFFull) != 0;
+            const bool kept = up ? (odd || m == kM - 1) : even;
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                kf[s][m] = buffer_load_b128(base, kept && t0 + tk0 + 8 * s < t_end ? k_lane + 256u * s : kOutOfRange);
+        }
+        // V^T operands
+        u32x4_t vf[kDB];
+        {
+            const char* base = reinterpret_cast<const char*>(vb + int64_t(t0 - tb) * D);
+            const bool in = t0 + 16 * up < n_k;
+#pragma unroll
+            for (int i = 0; i < kDB; ++i)
+                vf[i] = buffer_load_b128(base, in ? uint32_t(up) * uint32_t(D * 32) + v_off + 512u * i : kOutOfRange);
+        }
+        if constexpr (kRot) {
+            const float ub = rope::revolutions(uint32_t(t0), my_rho);
+            float* const blk = &s_blkcs[wave * D];
+            if (lane < kHalf) {
+                blk[2 * lane] = __builtin_amdgcn_cosf(ub);
+                blk[2 * lane + 1] = __builtin_amdgcn_sinf(ub);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int m = 0; m < kM; ++m) {
+                if (m == kM - 1 || ((keep >> (16 * m)) & 0xFFFFull) != 0) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+                        kf[s][m] = rope::rotate_block16(kf[s][m], hf, &s_colcs[(tk0 + 8 * s) * kCStride + 16 * (2 * m + up)],
+                                                        blk + 16 * (2 * m + up));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (full != q_full) {
+            q_full = full;
+#pragma unroll
+            for (int m = 0; m < kM; ++m) {
+                const uint32_t e8 = uint32_t(full >> (16 * m)) & 0xFFu, o8 = uint32_t(full >> (16 * m + 8)) & 0xFFu;
+                qm[m] = keep_pairs(q_frag(m), up ? o8 : e8);
+            }
+        }
+        f32x4_t sacc[2];
+#pragma unroll
+        for (int m = kM - 1; m >= 0; --m) {
+            if (m == kM - 1) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) sacc[s] = mfma16(kf[s][m], qm[m], f32x4_t{0.f, 0.f, 0.f, 0.f});
+            } else if ((full >> (16 * m)) & 0xFFFFull) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) sacc[s] = mfma16(kf[s][m], qm[m], sacc[s]);
+            }
+        }
+        uint64_t part = keep & ~full;
+        while (part) {
+            const int r = __builtin_ctzll(part);
+            const int c = r >> 3;
+            const int wr = __builtin_amdgcn_readlane(my_w, r);
+            const uint64_t grp = __ballot(my_w == wr) & part & (0xFFull << (8 * c));
+            part &= ~grp;
+            const u32x4_t q = keep_pairs(q_frag(c >> 1), up == (c & 1) ? uint32_t(grp >> (8 * c)) : 0u);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                u32x4_t kc = kf[s][0];
+#pragma unroll
+                for (int m = 1; m < kM; ++m)
+                    if (m == c >> 1) kc = kf[s][m];
+                const f32x4_t t = mfma16(kc, q, f32x4_t{0.f, 0.f, 0.f, 0.f});
+                const int thr = q_pos - (t0 + 16 * up + 8 * s + 4 * hf) - wr;  // keep iff v >= thr
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sacc[s][v] += v >= thr ? t[v] : 0.f;
+            }
+        }
+        if (t0 + 32 > t_end) {
+            // tokens past the split's end; V slots of tokens past the row's keys
+            const int bound = t_end - (t0 + 16 * up + 4 * hf);
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (8 * s + v >= bound) sacc[s][v] = -INFINITY;
+            const int lim = n_k - (t0 + 16 * up + 4 * hf);  // slot e valid iff 8(e/4) + e%4 < lim
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int e0 = 2 * t, e1 = 2 * t + 1;
+                const uint32_t msk = (8 * (e0 / 4) + e0 % 4 < lim ? 0x0000FFFFu : 0u) |
+                                     (8 * (e1 / 4) + e1 % 4 < lim ? 0xFFFF0000u : 0u);
+#pragma unroll
+                for (int i = 0; i < kDB; ++i) vf[i][t] &= msk;
+            }
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mx = fmaxf(mx, sacc[s][v]);
+        if (__any(mx * sc > m_thr)) {
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m_run, mx * sc);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = exp2_fast(m_run - m_use);
+            m_run = m_new;
+            m_thr = m_new + kRescale;
+            m_neg = -m_use;
+            l_run *= alpha;
+#pragma unroll
+            for (int i = 0; i < kDB; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) oacc[i][v] *= alpha;
+        }
+        u32x4_t pb;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float a = exp2_fast(__builtin_fmaf(sacc[s][2 * t], sc, m_neg));
+                const float c2 = exp2_fast(__builtin_fmaf(sacc[s][2 * t + 1], sc, m_neg));
+                l_run += a;
+                l_run += c2;
+                bf16x2_t two;
+                two[0] = (__bf16)a;
+                two[1] = (__bf16)c2;
+                pb[2 * s + t] = __builtin_bit_cast(uint32_t, two);
+            }
+#pragma unroll
+        for (int i = 0; i < kDB; ++i) oacc[i] = mfma16(vf[i], pb, oacc[i]);
+    }
+
+    // ---- combine the four waves' states (in wave order) and write the split's partial
+    float l_lane = l_run + __shfl_xor(l_run, 16);
+    l_lane += __shfl_xor(l_lane, 32);
+    if (g4 == 0) {
+        red_m[wave][r16] = m_run;
+        red_l[wave][r16] = l_lane;
+    }
+    __syncthreads();
+    float m_all = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, red_m[w][r16]);
+    const float f = m_run == -INFINITY ? 0.f : exp2_fast(m_run - m_all);
+    if (head_ok) {
+#pragma unroll
+        for (int i = 0; i < kDB; ++i) {
+            const f32x4_t o = oacc[i] * f;
+            *reinterpret_cast<f32x4_t*>(&red_o[(16 * wave + r16) * kOStride + 16 * i + 4 * g4]) = o;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < NH * (D / 4); e += kWaves * 64) {
+        const int h = e / (D / 4), x = 4 * (e % (D / 4));
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, red_m[w][h]);
+        f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) o += *reinterpret_cast<const f32x4_t*>(&red_o[(16 * w + h) * kOStride + x]);
+        const int64_t slot = p.n_k_rows != nullptr ? slot0 + h : slot0 + int64_t(h) * p.splits;
+        if (x == 0) {
+            float L = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                if (red_m[w][h] != -INFINITY) L += red_l[w][h] * exp2_fast(red_m[w][h] - M);
+            p.ws_m[slot] = M;
+            p.ws_l[slot] = L;
+        }
+        *reinterpret_cast<f32x4_t*>(&p.ws_o[slot * D + x]) = o;
+    }
+}
+
 // Merge of the split partials of one (batch, head) and 32 output dims: 256 threads.
 // The weights take one state per thread; the output sums take 8 quads of 4 dims x 32
 // state lanes, each lane reading 16 bytes per state, so that all of a thread's loads
@@ -607,7 +941,13 @@ hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     const bool ragged = p.n_k_rows != nullptr;
     const dim3 grid(unsigned(ragged ? p.splits + p.batch : p.splits),
                     unsigned(p.h_kv * (p.group / p.heads_per_block)), unsigned(ragged ? 1 : p.batch));
-    if (p.rotate)
+    // (the 16-column kernel's lane offsets reach over one chunk's stream in 32 bits)
+    if (p.heads_per_block <= 16 && p.cache_tokens < (1 << 27) - 64) {
+        if (p.rotate)
+            hipLaunchKernelGGL((decode_split16_kernel<D, true>), grid, dim3(kWaves * 64), 0, stream, p);
+        else
+            hipLaunchKernelGGL((decode_split16_kernel<D, false>), grid, dim3(kWaves * 64), 0, stream, p);
+    } else if (p.rotate)
         hipLaunchKernelGGL((decode_split_kernel<D, true>), grid, dim3(kWaves * 64), 0, stream, p);
     else
         hipLaunchKernelGGL((decode_split_kernel<D, false>), grid, dim3(kWaves * 64), 0, stream, p);

@@ -74,10 +74,23 @@ __device__ __forceinline__ u32x4_t other_half(u32x4_t x, int hh) {
     return r;
 }
 
+// The same where lanes l and l ^ 16 hold the two halves.
+__device__ __forceinline__ u32x4_t other_half16(u32x4_t x, int hh) {
+    u32x4_t r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        // odd 16-lane rows of the first copy trade places with even rows of the second
+        const auto sw = __builtin_amdgcn_permlane16_swap(x[t], x[t], false, false);
+        r[t] = hh ? sw[0] : sw[1];
+    }
+    return r;
+}
+
 // Rotate one fragment of a 32-token block by angle addition: `colcs` the (cos, sin) of the
 // token's offset in the block, `blkcs` of the block's first position, for the fragment's 8
-// pairs (16-byte aligned).  Every lane of the wave must execute it.
-__device__ __forceinline__ u32x4_t rotate_block(u32x4_t own, int hh, const float* colcs, const float* blkcs) {
+// pairs (16-byte aligned).
+__device__ __forceinline__ u32x4_t rotate_sum(u32x4_t own, u32x4_t other, int hh, const float* colcs,
+                                              const float* blkcs) {
     float cs8[8], sn8[8];
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
@@ -92,7 +105,16 @@ __device__ __forceinline__ u32x4_t rotate_block(u32x4_t own, int hh, const float
             sn8[e] = __builtin_fmaf(sB, cC, cB * sC);
         }
     }
-    return rotate_cs(own, other_half(own, hh), hh, cs8, sn8);
+    return rotate_cs(own, other, hh, cs8, sn8);
+}
+
+// The same with the other half taken from lane l ^ 32, or (rotate_block16) l ^ 16.  Every
+// lane of the wave must execute them.
+__device__ __forceinline__ u32x4_t rotate_block(u32x4_t own, int hh, const float* colcs, const float* blkcs) {
+    return rotate_sum(own, other_half(own, hh), hh, colcs, blkcs);
+}
+__device__ __forceinline__ u32x4_t rotate_block16(u32x4_t own, int hh, const float* colcs, const float* blkcs) {
+    return rotate_sum(own, other_half16(own, hh), hh, colcs, blkcs);
 }
 
 }  // namespace rope

@@ -1,0 +1,71 @@
+"""Decode at the edges of its two split kernels: up to 16 query heads per KV head are the
+columns of 16x16 matrix tiles, 17 to 32 of 32x32 ones.  Key counts lie at the edges of the
+8-, 16- and 32-token groups, windows end inside either chunk of a chunk pair (a table that is
+not monotone prunes the upper chunk and keeps the lower one), the caches past n_k hold NaN;
+pre-rotated and unrotated caches, against the oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from conftest import gpu_available
+import oracle
+import workloads as W
+from parity import compare, note, pack_kcache, pack_vcache, to_f64, windows_for
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+DEV = "cuda"
+
+CASES = [
+    # group, h_kv, n_k, q_pos, d, k, table ("base" or "mixed")
+    (1, 2, 7, 6, 64, 2.0, "base"),
+    (16, 1, 9, 8, 128, 2.0, "base"),
+    (16, 2, 17, 16, 64, math.inf, "base"),
+    (15, 1, 127, 126, 128, 2.0, "base"),
+    (3, 3, 129, 128, 64, 2.0, "mixed"),
+    (7, 1, 641, 640, 128, 2.0, "mixed"),
+    (5, 1, 1000, 700, 128, 0.5, "base"),      # keys past the query
+    (18, 1, 641, 640, 128, 2.0, "mixed"),
+    (32, 1, 129, 200, 64, 2.0, "base"),       # query past the cache's end
+]
+
+
+@pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(x) for x in c))
+def test_decode_columns(case, unrotated):
+    import paper_2608_02947_amd as atf
+    G, h_kv, n_k, q_pos, d, kwin, table = case
+    B, h_q, cap, base = 2, G * h_kv, n_k + 21, 1e4
+    g = torch.Generator(device="cpu").manual_seed(G * 1009 + n_k)
+    q = torch.randn((B, 1, h_q, d), generator=g).to(torch.bfloat16)
+    k = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    v = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    th = W.rope_theta(d, base)
+    if table == "mixed":
+        # thresholds rise and fall from chunk to chunk: 3 to 600 tokens at k = 2
+        th = torch.tensor(np.random.default_rng(7).uniform(0.02, 4.0, d // 2)) * \
+            torch.tensor([1.0, 6.0]).repeat_interleave(8).repeat(d // 32).double()
+    theta = th.numpy() if table == "mixed" else None
+    win, widths = windows_for(d, base, kwin, theta, n_ctx=max(n_k, q_pos + 1))
+    qr = W.rotate_half(q, torch.tensor([q_pos]), th)
+    kr = W.rotate_half(k, torch.arange(n_k), th)
+    o_ref, lse_ref, _ = oracle.attend(qr, kr, v, q_pos, widths)
+
+    def cache(x, pack):
+        full = torch.full((B, cap, h_kv, d), float("nan"), dtype=torch.bfloat16)
+        full[:, :n_k] = x
+        return pack(full.to(DEV))
+
+    kp, vp = cache(k if unrotated else kr, pack_kcache), cache(v, pack_vcache)
+    qd = (q if unrotated else qr)[:, 0].contiguous().to(DEV)
+    ws = torch.full((atf.atf_decode_workspace_bytes(B, h_q, h_kv, n_k, d),), 255, dtype=torch.uint8, device=DEV)
+    o = torch.full_like(qd, float("nan"))
+    lse = torch.full((B, h_q), float("nan"), dtype=torch.float32, device=DEV)
+    note(f"decode columns {case} unrotated={unrotated}")
+    fn = atf.atf_decode_unrotated if unrotated else atf.atf_decode
+    fn(qd, kp, vp, o, lse, q_pos, win, ws, n_k=n_k)
+    torch.cuda.synchronize()
+    compare(to_f64(o), to_f64(lse), o_ref[:, 0], lse_ref[:, :, 0], f"columns {case}")

@@ -31,7 +31,7 @@ struct PrefillParams {
     int32_t cache_tokens;  // tokens each cache entry is allocated for (>= n_k)
     int32_t pos_per_tile;  // query positions per workgroup (rows = positions x group)
     int32_t n_qtiles;
-    int32_t mono;        // thresholds non-decreasing and the last chunk kept at every distance
+    int32_t mono;        // thresholds non-decreasing in r
     float scale_log2;    // softmax scale * log2(e)
     WindowTable win;
 };

@@ -498,24 +498,45 @@ prefill_kernel(const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p
             // one MFMA per group, added where z <= W_r (register v holds distance
             // zbase - off(v): keep iff off(v) >= thr).  A table whose chunks share one
             // threshold (the rounded slice) needs one MFMA per partial chunk.
-            uint64_t part = keep & ~full;
-            while (part) {
-                const int r = __builtin_ctzll(part);
-                const int c = r >> 3;
-                const int wr = p.win.W[r];
-                const uint64_t grp = __ballot(my_w == wr) & part & (0xFFull << (8 * c));
-                part &= ~grp;
-                u32x4_t qc = qf[0];
-#pragma unroll
-                for (int cc = 1; cc < C::kChunks; ++cc)
-                    if (cc == c) qc = qf[cc];
-                const f32x16_t pr = mfma(lds_read_b128(kr + 2048u * c),
-                                         keep_pairs(qc, uint32_t(grp >> (8 * c))), zero16());
+            const auto add_kept = [&](u32x4_t k, u32x4_t q, uint32_t pairs, int wr) __attribute__((always_inline)) {
+                const f32x16_t pr = mfma(k, keep_pairs(q, pairs), zero16());
                 const int thr = my_pos - jb - 4 * hh - wr;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int off = 8 * (v / 4) + (v % 4);
                     acc[v] += off >= thr ? pr[v] : 0.f;
+                }
+            };
+            uint64_t part = keep & ~full;
+            if constexpr (D == 64) {
+                // chunk by chunk, the operands named at compile time: selecting them by a
+                // run-time chunk and re-reading K made a general tile 2.3 times a uniform
+                // one (16/16 heads, 8,191 tokens, base 1e4: 222 us, now 207; rounded slice
+                // 150).  At d = 128 the eight copies cost 1-2 % from 32K tokens.
+                if (part) {
+#pragma unroll
+                    for (int c = 0; c < C::kChunks; ++c) {
+                        uint32_t pc = uint32_t(part >> (8 * c)) & 0xFFu;
+                        while (pc) {
+                            const int wr = __builtin_amdgcn_readlane(my_w, 8 * c + __builtin_ctz(pc));
+                            const uint32_t grp = uint32_t(__ballot(my_w == wr) >> (8 * c)) & pc;
+                            pc &= ~grp;
+                            add_kept(kf[c], qf[c], grp, wr);
+                        }
+                    }
+                }
+            } else {
+                while (part) {
+                    const int r = __builtin_ctzll(part);
+                    const int c = r >> 3;
+                    const int wr = p.win.W[r];
+                    const uint64_t grp = __ballot(my_w == wr) & part & (0xFFull << (8 * c));
+                    part &= ~grp;
+                    u32x4_t qc = qf[0];
+#pragma unroll
+                    for (int cc = 1; cc < C::kChunks; ++cc)
+                        if (cc == c) qc = qf[cc];
+                    add_kept(lds_read_b128(kr + 2048u * c), qc, uint32_t(grp >> (8 * c)), wr);
                 }
             }
             sacc[kb] = acc;
@@ -676,25 +697,27 @@ prefill_kernel(const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p
                 const uint64_t full = __ballot(my_w >= zhi);
                 const uint64_t keep = __ballot(my_w >= zlo);
                 if (full == keep) {
-                    // uniform: kept pairs r >= rf (non-empty: the last chunk is kept at
-                    // every distance of the call).  The run lasts while the next
-                    // threshold below, W[rf - 1], stays under the tile's smallest
-                    // distance: wp_min - 64 u' - 63 > W[rf - 1].
-                    const int rf = __builtin_ctzll(full);
+                    // uniform: kept pairs r >= rf (rf = d/2: none, every score is 0; a
+                    // window that ends before the farthest key, base 1e4 at 20,000 tokens,
+                    // then has no general tile but those a threshold lies in: 4,000 rows
+                    // against 20,000 keys, 16/16 heads, 515 -> 345 us).  The
+                    // run lasts while the next threshold below, W[rf - 1], stays under the
+                    // tile's smallest distance: wp_min - 64 u' - 63 > W[rf - 1].
+                    const int rf = __popcll(~full & (~0ull >> (64 - C::kHalf)));
                     seg_end = n_tiles;
                     if (rf > 0) {
                         const int wlow = p.win.W[rf - 1];
                         const int64_t lim = (int64_t(wp_min) - kBN - wlow) / kBN + 1;
                         seg_end = int(max(int64_t(u) + 1, min(lim, int64_t(n_tiles))));
                     }
-                    mode = rf >> 3;
+                    mode = min(rf >> 3, C::kChunks - 1);
                     if (rf != qb_rf) {
                         qb_rf = rf;
                         u32x4_t qs = qf[0];
 #pragma unroll
                         for (int cc = 1; cc < C::kChunks; ++cc)
-                            if (cc == (rf >> 3)) qs = qf[cc];
-                        qb = keep_pairs(qs, (0xFFu << (rf & 7)) & 0xFFu);
+                            if (cc == mode) qs = qf[cc];
+                        qb = keep_pairs(qs, uint32_t(full >> (8 * mode)) & 0xFFu);
                     }
                 }
             }
@@ -705,7 +728,7 @@ prefill_kernel(const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p
         if constexpr (CFV < C::kChunks) {                                                       \
             for (; u < seg_end; ++u)                                                            \
                 run_tile(u, [&](int t) __attribute__((always_inline)) { qk_uniform(t, std::integral_constant<int, CFV>{}); }); \
-        } else { /* not reached: rf < d/2 - 8 */                                                \
+        } else { /* not reached: mode < d/16 */                                                 \
             run_tile(u, [&](int t) __attribute__((always_inline)) { qk_general(t); });                                         \
             ++u;                                                                                \
         }                                                                                       \
@@ -1108,13 +1131,12 @@ __global__ __launch_bounds__(S * 64, 2) void prefill_short_kernel(
 template <class P>
 hipError_t prepare(P& p, int head_dim, unsigned* blocks, bool* window_on) {
     // the window is off when no threshold is below the largest possible distance;
-    // the uniform-run path needs thresholds non-decreasing in r and the last chunk
-    // kept at every distance of the call
+    // the uniform-run path needs thresholds non-decreasing in r
     const int64_t max_dist = int64_t(p.q_pos0) + p.n_q - 1;
     bool on = false;
     for (int r = 0; r < head_dim / 2; ++r)
         if (int64_t(p.win.W[r]) < max_dist) on = true;
-    bool mono = int64_t(p.win.W[head_dim / 2 - kChunkPairs]) >= max_dist;
+    bool mono = true;
     for (int r = 1; r < head_dim / 2; ++r)
         if (p.win.W[r] < p.win.W[r - 1]) mono = false;
     p.mono = mono ? 1 : 0;
@@ -1142,8 +1164,9 @@ hipError_t prepare(P& p, int head_dim, unsigned* blocks, bool* window_on) {
 // to 5,000 rows, 512 to 40,000 keys)
 //   d = 128, windowed: 1.30 at x = 97..116, 1.04-1.18 at 132..145, 0.93-1.06 at 146..173
 //   d = 128, off:      1.17-1.18 at 98..116, 0.96-1.09 at 120..132, 0.82-0.95 at 146..173
-//   d = 64, windowed (128-row workgroups): 1.26 at 241, 1.23-1.29 at 278..320
-//   d = 64, off: 1.43 at 139, 1.28 at 160
+//   d = 64, windowed (128-row workgroups): 1.26 at 241, 1.23-1.29 at 278..320, 0.92-1.07 at
+//   362..402
+//   d = 64, off: 1.43 at 139, 1.28 at 160, 1.06-1.16 at 181, 0.93-0.98 at 201..228
 // and where keys are rotated as they are read (every row block turns its own keys)
 //   d = 128: windowed 1.29-1.55 at 52..63, 0.80-1.02 at 84..98; off 1.03-1.11 at 52..58,
 //   0.79-0.90 at 67..72;  d = 64: windowed 1.14-1.63 at 167..200, 0.90-1.03 at 223..241;
@@ -1158,7 +1181,7 @@ int short_split(const PrefillParams& p, int head_dim, bool window_on, bool rotat
     if (int64_t(p.cache_tokens) * head_dim * 2 > int64_t(UINT32_MAX)) return 0;
     const int64_t longest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + p.n_q);
     const int64_t shortest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + 1);
-    const int64_t limit = head_dim == 64 ? (window_on ? (rotate ? 192 : 320) : (rotate ? 80 : 160))
+    const int64_t limit = head_dim == 64 ? (window_on ? (rotate ? 192 : 320) : (rotate ? 80 : 184))
                                          : (rotate ? (window_on ? 64 : 56) : (window_on ? 132 : 120));
     if (blocks * ((shortest + longest) / 2) > limit * longest) return 0;
     const int64_t row_blocks = blocks * (head_dim == 64 && window_on ? 4 : 8);

@@ -35,6 +35,9 @@ CASES = [
     (9, 4129, 4120, 7, 1, 128, 1e7, 2.0, 0),      # 8 waves, ragged
     (3, 4200, 4190, 16, 2, 64, 1e4, math.inf, 0),  # 8 waves, keys past the last query
     (20, 4100, 4300, 4, 1, 128, 1e4, 2.0, 8),     # 8 waves, keys end before every query
+    (40, 2100, 2060, 7, 1, 64, 100.0, 2.0, 0),    # every window ends inside the keys: far tiles keep no pair
+    (33, 2100, 2067, 4, 1, 128, 100.0, 2.0, 0),   # the same at d = 128
+    (70, 700, 630, 2, 2, 64, 100.0, 2.0, 8),      # and with the rounded slice
 ]
 
 

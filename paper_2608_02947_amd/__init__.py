@@ -144,6 +144,21 @@ _PROFILE_KINDS = {"constant": ATF_PROFILE_CONSTANT, "arithmetic": ATF_PROFILE_AR
                   "geometric": ATF_PROFILE_GEOMETRIC}
 
 
+_UNKNOWN = object()
+
+
+def _values(x):
+    """A copy of the values of an optional sequence of floats, or _UNKNOWN for a type whose
+    values are not read here."""
+    if x is None:
+        return None
+    if type(x) is list or type(x) is tuple:
+        return tuple(x)
+    if type(x) is np.ndarray:
+        return x.dtype.str, x.shape, x.tobytes()
+    return _UNKNOWN
+
+
 @dataclasses.dataclass
 class Window:
     """atf_window: d, RoPE base B, retained periods k (+inf = off), optional theta'_r.
@@ -171,6 +186,24 @@ class Window:
                 or self.beta != 0.0 or self.cap != math.inf)
 
     def as_c(self):
+        """(C struct, the arrays it points to).  Both are kept with the values they were made
+        from and used again while every field still holds those values (converting two
+        lists of 64 frequencies took 6 of the 15 us a decode call spends on the host)."""
+        now = (self.head_dim, self.rope_base, self.k, self.gamma, self.a, self.beta, self.cap,
+               self.slice_pairs, _values(self.inv_freq), _values(self.k_profile))
+        kept = self.__dict__.get("_c")
+        if kept is not None and kept[0] == now:
+            return kept[1]
+        c = self._make_c()
+        if now[8] is not _UNKNOWN and now[9] is not _UNKNOWN:
+            self.__dict__["_c"] = (now, c)
+        return c
+
+    def __getstate__(self):
+        # (a copied or pickled window makes its own C struct)
+        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+
+    def _make_c(self):
         def arr(x):
             if x is None:
                 return None
@@ -234,19 +267,24 @@ def _dev_ptr(t, dtype, name):
     torch = _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
+    if t.is_cuda and t.dtype is dtype and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must be on the GPU")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    # the handle of torch.cuda.current_stream() without the Stream object around it (8 us)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def kcache_shape(batch: int, cache_tokens: int, h_kv: int, head_dim: int):
@@ -266,9 +304,9 @@ def atf_prefill(q, k_cache, v_cache, o, lse, q_pos0: int, window: Window,
         raise ValueError("atf_prefill: k_cache must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_cache.shape
     n_k = cap if n_k is None else int(n_k)
-    if tuple(k_cache.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_cache.shape) != vcache_shape(B, cap, h_kv, d) or \
-            tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q, n_q):
+    if k_cache.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_cache.shape != vcache_shape(B, cap, h_kv, d) or \
+            o.shape != q.shape or lse.shape != (B, h_q, n_q):
         raise ValueError("atf_prefill: inconsistent shapes")
     cw, keep = window.as_c()
     rc = _lib.atf_prefill(_dev_ptr(q, torch.bfloat16, "q"), _dev_ptr(k_cache, torch.bfloat16, "k"),
@@ -306,9 +344,9 @@ def atf_cache_append(k_new, v_new, k_cache, v_cache, pos0: int, stream=None):
     if k_cache.dim() != 5:
         raise ValueError("atf_cache_append: k_cache must be [B, h_kv, d/16, C, 16]")
     cap = k_cache.shape[3]
-    if tuple(v_new.shape) != tuple(k_new.shape) or \
-            tuple(k_cache.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_cache.shape) != vcache_shape(B, cap, h_kv, d):
+    if v_new.shape != k_new.shape or \
+            k_cache.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_cache.shape != vcache_shape(B, cap, h_kv, d):
         raise ValueError("atf_cache_append: inconsistent shapes")
     _check(_lib.atf_cache_append(_dev_ptr(k_new, torch.bfloat16, "k_new"),
                                  _dev_ptr(v_new, torch.bfloat16, "v_new"),
@@ -321,7 +359,7 @@ def atf_pack_vcache(v_bshd, v_pack, stream=None):
     """v_bshd [B, n_k, h_kv, d] -> v_pack [B, h_kv, ceil(n_k/16), d, 16] (bf16)."""
     torch = _torch()
     B, n_k, h_kv, d = v_bshd.shape
-    if tuple(v_pack.shape) != vcache_shape(B, n_k, h_kv, d):
+    if v_pack.shape != vcache_shape(B, n_k, h_kv, d):
         raise ValueError("atf_pack_vcache: destination shape mismatch")
     _check(_lib.atf_pack_vcache(_dev_ptr(v_bshd, torch.bfloat16, "v_bshd"),
                                 _dev_ptr(v_pack, torch.bfloat16, "v_pack"), B, n_k, h_kv, d,
@@ -340,9 +378,9 @@ def atf_decode(q, k_pcm, v_pack, o, lse, q_pos: int, window: Window, workspace,
         raise ValueError("atf_decode: k_pcm must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_pcm.shape
     n_k = cap if n_k is None else int(n_k)
-    if tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
-            tuple(k_pcm.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_pack.shape) != vcache_shape(B, cap, h_kv, d):
+    if o.shape != q.shape or lse.shape != (B, h_q) or \
+            k_pcm.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_pack.shape != vcache_shape(B, cap, h_kv, d):
         raise ValueError("atf_decode: inconsistent shapes")
     cw, keep = window.as_c()
     rc = _lib.atf_decode(_dev_ptr(q, torch.bfloat16, "q"), _dev_ptr(k_pcm, torch.bfloat16, "k"),
@@ -368,9 +406,9 @@ def atf_decode_noalloc(q, k_pcm, v_pack, o, lse, q_pos: int, window: Window,
         raise ValueError("atf_decode_noalloc: k_pcm must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_pcm.shape
     n_k = cap if n_k is None else int(n_k)
-    if tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
-            tuple(k_pcm.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_pack.shape) != vcache_shape(B, cap, h_kv, d):
+    if o.shape != q.shape or lse.shape != (B, h_q) or \
+            k_pcm.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_pack.shape != vcache_shape(B, cap, h_kv, d):
         raise ValueError("atf_decode_noalloc: inconsistent shapes")
     cw, keep = window.as_c()
     rc = _lib.atf_decode_noalloc(_dev_ptr(q, torch.bfloat16, "q"),
@@ -399,7 +437,7 @@ def atf_rotate_kcache(k_pcm, k_rot, window: Window, n_k: Optional[int] = None,
     position t, for t < n_k (default C); later slots of k_rot are not written.  k_rot may
     be k_pcm itself (in place)."""
     torch = _torch()
-    if k_pcm.dim() != 5 or tuple(k_rot.shape) != tuple(k_pcm.shape):
+    if k_pcm.dim() != 5 or k_rot.shape != k_pcm.shape:
         raise ValueError("atf_rotate_kcache: caches must both be [B, h_kv, d/16, C, 16]")
     B, h_kv, nc, cap, _ = k_pcm.shape
     d = 16 * nc
@@ -417,11 +455,11 @@ def atf_cache_append_rotated(k_new, v_new, k_cache, v_cache, pos0: int, window: 
     position pos0 + t as it is written.  k_new, v_new [B, n_new, h_kv, d] bf16."""
     torch = _torch()
     B, n_new, h_kv, d = k_new.shape
-    if k_cache.dim() != 5 or tuple(v_new.shape) != tuple(k_new.shape):
+    if k_cache.dim() != 5 or v_new.shape != k_new.shape:
         raise ValueError("atf_cache_append_rotated: inconsistent shapes")
     cap = k_cache.shape[3]
-    if tuple(k_cache.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_cache.shape) != vcache_shape(B, cap, h_kv, d):
+    if k_cache.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_cache.shape != vcache_shape(B, cap, h_kv, d):
         raise ValueError("atf_cache_append_rotated: inconsistent cache shapes")
     cw, keep = window.as_c()
     fp, keep2 = _rope_freq(rope_inv_freq, d)
@@ -444,9 +482,9 @@ def atf_prefill_unrotated(q, k_cache, v_cache, o, lse, q_pos0: int, window: Wind
         raise ValueError("atf_prefill_unrotated: k_cache must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_cache.shape
     n_k = cap if n_k is None else int(n_k)
-    if tuple(k_cache.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_cache.shape) != vcache_shape(B, cap, h_kv, d) or \
-            tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q, n_q):
+    if k_cache.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_cache.shape != vcache_shape(B, cap, h_kv, d) or \
+            o.shape != q.shape or lse.shape != (B, h_q, n_q):
         raise ValueError("atf_prefill_unrotated: inconsistent shapes")
     cw, keep = window.as_c()
     fp, keep2 = _rope_freq(rope_inv_freq, d)
@@ -470,9 +508,9 @@ def atf_decode_unrotated(q, k_pcm, v_pack, o, lse, q_pos: int, window: Window, w
         raise ValueError("atf_decode_unrotated: k_pcm must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_pcm.shape
     n_k = cap if n_k is None else int(n_k)
-    if tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
-            tuple(k_pcm.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_pack.shape) != vcache_shape(B, cap, h_kv, d):
+    if o.shape != q.shape or lse.shape != (B, h_q) or \
+            k_pcm.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_pack.shape != vcache_shape(B, cap, h_kv, d):
         raise ValueError("atf_decode_unrotated: inconsistent shapes")
     cw, keep = window.as_c()
     fp, keep2 = _rope_freq(rope_inv_freq, d)
@@ -497,10 +535,10 @@ def atf_decode_ragged(q, k_pcm, v_pack, o, lse, n_k_rows, q_pos_rows, max_n_k: i
     if k_pcm.dim() != 5:
         raise ValueError("atf_decode_ragged: k_pcm must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_pcm.shape
-    if tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
-            tuple(k_pcm.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_pack.shape) != vcache_shape(B, cap, h_kv, d) or \
-            tuple(n_k_rows.shape) != (B,) or tuple(q_pos_rows.shape) != (B,):
+    if o.shape != q.shape or lse.shape != (B, h_q) or \
+            k_pcm.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_pack.shape != vcache_shape(B, cap, h_kv, d) or \
+            n_k_rows.shape != (B,) or q_pos_rows.shape != (B,):
         raise ValueError("atf_decode_ragged: inconsistent shapes")
     cw, keep = window.as_c()
     rc = _lib.atf_decode_ragged(
@@ -528,8 +566,8 @@ def _pages(k_pages, v_pages, fn):
         raise ValueError(f"{fn}: page pools must be 5-d (see kpages_shape, vpages_shape)")
     num_pages, h_kv, c16, pt, _ = k_pages.shape
     d = 16 * c16
-    if tuple(k_pages.shape) != kpages_shape(num_pages, pt, h_kv, d) or \
-            tuple(v_pages.shape) != vpages_shape(num_pages, pt, h_kv, d):
+    if k_pages.shape != kpages_shape(num_pages, pt, h_kv, d) or \
+            v_pages.shape != vpages_shape(num_pages, pt, h_kv, d):
         raise ValueError(f"{fn}: inconsistent page pool shapes")
     return num_pages, h_kv, pt, d
 
@@ -540,7 +578,7 @@ def atf_cache_append_paged(k_new, v_new, k_pages, v_pages, block_table, pos0: in
     torch = _torch()
     num_pages, h_kv, pt, d = _pages(k_pages, v_pages, "atf_cache_append_paged")
     B, n_new, hk, dd = k_new.shape
-    if tuple(v_new.shape) != tuple(k_new.shape) or hk != h_kv or dd != d or \
+    if v_new.shape != k_new.shape or hk != h_kv or dd != d or \
             block_table.dim() != 2 or block_table.shape[0] != B:
         raise ValueError("atf_cache_append_paged: inconsistent shapes")
     rc = _lib.atf_cache_append_paged(
@@ -558,7 +596,7 @@ def atf_cache_append_paged_rotated(k_new, v_new, k_pages, v_pages, block_table, 
     torch = _torch()
     num_pages, h_kv, pt, d = _pages(k_pages, v_pages, "atf_cache_append_paged_rotated")
     B, n_new, hk, dd = k_new.shape
-    if tuple(v_new.shape) != tuple(k_new.shape) or hk != h_kv or dd != d or \
+    if v_new.shape != k_new.shape or hk != h_kv or dd != d or \
             block_table.dim() != 2 or block_table.shape[0] != B or window.head_dim != d:
         raise ValueError("atf_cache_append_paged_rotated: inconsistent shapes")
     cw, keep = window.as_c()
@@ -578,9 +616,9 @@ def atf_decode_paged(q, k_pages, v_pages, o, lse, block_table, n_k_rows, q_pos_r
     torch = _torch()
     num_pages, h_kv, pt, d = _pages(k_pages, v_pages, "atf_decode_paged")
     B, h_q, dq = q.shape
-    if dq != d or tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
+    if dq != d or o.shape != q.shape or lse.shape != (B, h_q) or \
             block_table.dim() != 2 or block_table.shape[0] != B or \
-            tuple(n_k_rows.shape) != (B,) or tuple(q_pos_rows.shape) != (B,):
+            n_k_rows.shape != (B,) or q_pos_rows.shape != (B,):
         raise ValueError("atf_decode_paged: inconsistent shapes")
     cw, keep = window.as_c()
     rc = _lib.atf_decode_paged(
@@ -604,10 +642,10 @@ def atf_decode_ragged_unrotated(q, k_pcm, v_pack, o, lse, n_k_rows, q_pos_rows, 
     if k_pcm.dim() != 5:
         raise ValueError("atf_decode_ragged_unrotated: k_pcm must be [B, h_kv, d/16, C, 16]")
     _, h_kv, _, cap, _ = k_pcm.shape
-    if tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
-            tuple(k_pcm.shape) != kcache_shape(B, cap, h_kv, d) or \
-            tuple(v_pack.shape) != vcache_shape(B, cap, h_kv, d) or \
-            tuple(n_k_rows.shape) != (B,) or tuple(q_pos_rows.shape) != (B,):
+    if o.shape != q.shape or lse.shape != (B, h_q) or \
+            k_pcm.shape != kcache_shape(B, cap, h_kv, d) or \
+            v_pack.shape != vcache_shape(B, cap, h_kv, d) or \
+            n_k_rows.shape != (B,) or q_pos_rows.shape != (B,):
         raise ValueError("atf_decode_ragged_unrotated: inconsistent shapes")
     cw, keep = window.as_c()
     fp, keep2 = _rope_freq(rope_inv_freq, d)
@@ -629,9 +667,9 @@ def atf_decode_paged_unrotated(q, k_pages, v_pages, o, lse, block_table, n_k_row
     torch = _torch()
     num_pages, h_kv, pt, d = _pages(k_pages, v_pages, "atf_decode_paged_unrotated")
     B, h_q, dq = q.shape
-    if dq != d or tuple(o.shape) != tuple(q.shape) or tuple(lse.shape) != (B, h_q) or \
+    if dq != d or o.shape != q.shape or lse.shape != (B, h_q) or \
             block_table.dim() != 2 or block_table.shape[0] != B or \
-            tuple(n_k_rows.shape) != (B,) or tuple(q_pos_rows.shape) != (B,):
+            n_k_rows.shape != (B,) or q_pos_rows.shape != (B,):
         raise ValueError("atf_decode_paged_unrotated: inconsistent shapes")
     cw, keep = window.as_c()
     fp, keep2 = _rope_freq(rope_inv_freq, d)

@@ -325,8 +325,8 @@ int rope_fractions(const char* fn, const atf_window* w, const double* inv_freq,
             return fail(ATF_EINVAL, "%s: rotation frequency %d = %g must be finite and >= 0", fn, r,
                         th);
         long double f = static_cast<long double>(th) / two_pi;
-        f -= std::floor(f);
-        long double scaled = std::ldexp(f, 64);
+        if (f >= 1.0L) f -= std::floor(f);
+        const long double scaled = f * 18446744073709551616.0L;  // 2^64: exact
         uint64_t fx = scaled >= 18446744073709551615.0L ? UINT64_MAX : static_cast<uint64_t>(scaled);
         rho_hi[r] = static_cast<uint32_t>(fx >> 32);
         rho_lo[r] = static_cast<uint32_t>(fx);

@@ -565,6 +565,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_split_kernel(const Deco
 // 8,200 keys, 24/8 heads 50.3 -> 41.6; 32,768 keys, 28/4 24.7 -> 17.6; 131,072 keys,
 // 16/16 heads of d = 64 90.3 -> 68.8; batch 40 up to 5,000 keys, 28/4, paged 43.4 -> 32.2;
 // 2^20 keys, 28/4 283.7 -> 273.3; rotating, batch 2 at 100,003 keys 77.9 -> 63.5.
+//
+// P enters the matrix tiles as two bf16 numbers, the one below its value and what is left
+// over: fewer, longer splits than the 32-column kernel's hold fewer probabilities that are
+// exactly 1 (each split's largest), and with one bf16 number the output's error against 64
+// bits, on average over random rows, rose with the length of a split (8 rows of 2,000 keys,
+// 24/8 heads 0.00189 -> 0.00212; 100,003 keys 0.00232).  With two it is 0.00166 at every
+// length, that of the output's own rounding.  The matrix units have the room: 2^20 keys, 28/4
+// heads 273.5 -> 274.8 us, 64 rows of 8,000 170.9 -> 171.1, rotating 2^20 keys 306 -> 303
+// (at most 3 % at d = 64, 14/2 heads, 64 rows of 8,000, rotating: 43.0 -> 44.4).
 template <int D, bool kRot>
 __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128 ? 3 : 4))) void decode_split16_kernel(const DecodeParams p) {
     constexpr int kChunks = D / 16;
@@ -803,7 +812,7 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
 #pragma unroll
                 for (int v = 0; v < 4; ++v) oacc[i][v] *= alpha;
         }
-        u32x4_t pb;
+        u32x4_t pb, pl;  // P in two bf16 numbers
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -812,13 +821,20 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
                 const float c2 = exp2_fast(__builtin_fmaf(sacc[s][2 * t + 1], sc, m_neg));
                 l_run += a;
                 l_run += c2;
-                bf16x2_t two;
-                two[0] = (__bf16)a;
-                two[1] = (__bf16)c2;
-                pb[2 * s + t] = __builtin_bit_cast(uint32_t, two);
+                // the bf16 number below P, and the rest, which is never 0 then (an infinite
+                // value times 0 would turn an infinite output into NaN)
+                const uint32_t ha = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, a), 1u) & 0xFFFF0000u;
+                const uint32_t hc = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, c2), 1u) & 0xFFFF0000u;
+                pb[2 * s + t] = ha >> 16 | hc;
+                bf16x2_t rest;
+                rest[0] = (__bf16)(a - __builtin_bit_cast(float, ha));
+                rest[1] = (__bf16)(c2 - __builtin_bit_cast(float, hc));
+                pl[2 * s + t] = __builtin_bit_cast(uint32_t, rest);
             }
 #pragma unroll
         for (int i = 0; i < kDB; ++i) oacc[i] = mfma16(vf[i], pb, oacc[i]);
+#pragma unroll
+        for (int i = 0; i < kDB; ++i) oacc[i] = mfma16(vf[i], pl, oacc[i]);
     }
 
     // ---- combine the four waves' states (in wave order) and write the split's partial

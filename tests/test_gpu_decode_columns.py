@@ -69,3 +69,30 @@ def test_decode_columns(case, unrotated):
     fn(qd, kp, vp, o, lse, q_pos, win, ws, n_k=n_k)
     torch.cuda.synchronize()
     compare(to_f64(o), to_f64(lse), o_ref[:, 0], lse_ref[:, :, 0], f"columns {case}")
+
+
+@pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])
+def test_decode_columns_infinite_value(unrotated):
+    """An infinite value makes its dimension's output infinite and leaves the others as they
+    are: no part of a probability may be 0 where the probability is not."""
+    import paper_2608_02947_amd as atf
+    n_k, h_q, h_kv, d = 2000, 7, 1, 128
+    g = torch.Generator(device="cpu").manual_seed(5)
+    q = torch.randn((1, h_q, d), generator=g).to(torch.bfloat16)
+    k = 0.1 * torch.randn((1, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    v = torch.randn((1, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    k[0, 0] = k[0, 37] = 0.0  # logits of 0: among them the first of a split
+    win, _ = windows_for(d, 1e4, 2.0, None, n_ctx=n_k)
+    ws = torch.zeros((atf.atf_decode_workspace_bytes(1, h_q, h_kv, n_k, d),), dtype=torch.uint8, device=DEV)
+    outs = []
+    for infinite in (False, True):
+        if infinite:
+            v[0, 0, 0, 3], v[0, 37, 0, 77], v[0, 1999, 0, 5] = math.inf, -math.inf, math.inf
+        o, lse = torch.zeros((1, h_q, d), dtype=torch.bfloat16, device=DEV), torch.zeros((1, h_q), device=DEV)
+        fn = atf.atf_decode_unrotated if unrotated else atf.atf_decode
+        fn(q.to(DEV), pack_kcache(k.to(DEV)), pack_vcache(v.to(DEV)), o, lse, n_k - 1, win, ws, n_k=n_k)
+        torch.cuda.synchronize()
+        outs.append(o[0].float().cpu())
+    want = outs[0].clone()
+    want[:, 3], want[:, 77], want[:, 5] = math.inf, -math.inf, math.inf
+    assert torch.equal(outs[1], want)

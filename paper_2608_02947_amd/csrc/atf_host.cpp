@@ -208,6 +208,28 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
     return static_cast<int32_t>(std::max<int64_t>(1, (steps + per - 1) / per));
 }
 
+// Whether a uniform batch takes one workgroup of 8 waves per (row, KV head), which writes the
+// output itself, and no merge.
+//
+// With 256 such workgroups or more every CU has one, and splitting only adds the partial
+// states' way through memory and the merge (us, split -> direct): 32 rows of 500 keys, 24/8
+// heads 19.8 -> 14.0, of 16,000 306 -> 295; rotating 23.9 -> 18.3, and 173 -> 155 at 8,000.
+// With 128 to 255 they win while a row is short: d = 128 39.3 -> 33.8 at 3,840 keys,
+// 62.3 -> 68.9 at 5,000 without a window; d = 64 39.5 -> 34.1 at 7,680, 60.4 -> 66.8 at 10,000;
+// rotating d = 128 18.8 -> 18.7 at 768, 21.2 -> 21.4 at 1,024, d = 64 14.2 -> 14.0 at 1,024,
+// 17.2 -> 18.2 at 1,500.  With fewer they win while a row costs less than the second launch:
+// d = 128 12.3 -> 11.5 at 1,280, 12.4 -> 12.3 at 1,600; d = 64 13.4 -> 10.8 at 2,048,
+// 13.2 -> 11.2 at 2,560, 13.6 -> 13.7 at 3,000; rotating d = 128 12.1 -> 10.5 at 256,
+// 12.0 -> 13.6 at 512, d = 64 13.5 -> 11.8 at 768, 13.3 -> 13.4 at 1,000.
+bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
+                   int32_t heads_per_block, bool rotate) {
+    if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
+    const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
+    if (cols >= 256) return true;
+    if (cols >= 128) return n_valid <= (rotate ? (head_dim == 64 ? 1024 : 768) : (head_dim == 64 ? 7680 : 3840));
+    return n_valid <= (rotate ? (head_dim == 64 ? 768 : 256) : (head_dim == 64 ? 2560 : 1280));
+}
+
 // Work items the keys of a ragged batch are spread over, at most the decode_ragged_items()
 // its workspace has room for.  1536 workgroups, two rounds of decode_split16_kernel's 768
 // (rows differ, so one round leaves the CUs of the short ones idle: 768 takes 1.08 times as
@@ -732,9 +754,11 @@ int decode_impl(const char* fn, const void* q, const void* k_cache, const void* 
     } else {
         const int64_t last = q_pos < n_k - 1 ? q_pos : n_k - 1;
         p.n_valid = static_cast<int32_t>(last + 1);
+        const bool direct = atf::decode_direct(batch, h_q, d, p.n_valid, cache_tokens, hpb, rope.rotate);
         const int32_t splits =
-            atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, rope.rotate);
+            direct ? 1 : atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, rope.rotate);
         p.splits = splits;
+        p.direct = direct;
         const auto step_of = [&](int64_t s) {
             const int64_t per = (p.n_valid + s - 1) / s;
             return (per + atf::kDecodeTokenStep - 1) / atf::kDecodeTokenStep * atf::kDecodeTokenStep;

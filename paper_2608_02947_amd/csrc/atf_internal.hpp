@@ -77,6 +77,7 @@ struct DecodeParams {
     // at position pos is rotated by pos * theta_r, with rho_r = theta_r / (2 pi) mod 1
     // as a 0.64 fixed-point fraction (hi and lo words)
     int32_t rotate;
+    int32_t direct;           // one split per row, which writes the output itself (no merge)
     uint32_t rope_rho_hi[kMaxPairs];
     uint32_t rope_rho_lo[kMaxPairs];
 };
@@ -124,6 +125,12 @@ int32_t decode_ragged_items(int32_t cols);
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
                            int32_t heads_per_block, bool rotate);
 int32_t decode_plan_items(int32_t cols, int32_t heads_per_block);
+// Whether a uniform batch runs without splits.
+bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
+                   int32_t heads_per_block, bool rotate);
+// Caches from this many tokens are out of the 32-bit lane offsets of decode_split16_kernel
+// (they reach over one chunk's stream) and take decode_split_kernel.
+constexpr int64_t kDecode16MaxTokens = (int64_t(1) << 27) - 64;
 // Tokens handled per decode workgroup iteration (the split granularity).
 constexpr int32_t kDecodeTokenStep = 128;
 // Largest split count the merge kernel accepts.

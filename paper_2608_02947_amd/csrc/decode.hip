@@ -51,6 +51,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
+constexpr int kDirectWaves = 8;  // of a workgroup that takes a whole row
 constexpr float kRescale = 8.0f;  // lazy-rescale threshold, log2 units
 
 __device__ __forceinline__ f32x16_t mfma(u32x4_t a, u32x4_t b, f32x16_t c) {
@@ -574,21 +575,24 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_split_kernel(const Deco
 // length, that of the output's own rounding.  The matrix units have the room: 2^20 keys, 28/4
 // heads 273.5 -> 274.8 us, 64 rows of 8,000 170.9 -> 171.1, rotating 2^20 keys 306 -> 303
 // (at most 3 % at d = 64, 14/2 heads, 64 rows of 8,000, rotating: 43.0 -> 44.4).
-template <int D, bool kRot>
-__global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128 ? 3 : 4))) void decode_split16_kernel(const DecodeParams p) {
+//
+// NW waves per workgroup: 4 where rows are split, kDirectWaves where a workgroup takes a
+// whole row (p.direct) and writes its output instead of a partial state.
+template <int D, bool kRot, int NW>
+__global__ __launch_bounds__(NW * 64, (NW > 4 ? 2 : kRot ? (D == 128 ? 2 : 3) : (D == 128 ? 3 : 4))) void decode_split16_kernel(const DecodeParams p) {
     constexpr int kChunks = D / 16;
     constexpr int kHalf = D / 2;
     constexpr int kM = D / 32;   // chunk pairs: K operands per 16 tokens
     constexpr int kDB = D / 16;  // 16-dim blocks of the output
     constexpr int kOStride = D + 4;
     constexpr int kCStride = D + 4;
-    __shared__ float red_m[kWaves][16];
-    __shared__ float red_l[kWaves][16];
+    __shared__ float red_m[NW][16];
+    __shared__ float red_l[NW][16];
     // while the waves stream: the queries, then (rotation) the (cos, sin) of t * theta_r for
     // the 32 tokens of a block and per wave those of the block's first position; afterwards
     // the waves' outputs [wave][head][D + 4]
-    constexpr int kTables = 8 * D + (kRot ? 32 * kCStride + kWaves * D : 0);
-    constexpr int kMerge = kWaves * 16 * kOStride;
+    constexpr int kTables = 8 * D + (kRot ? 32 * kCStride + NW * D : 0);
+    constexpr int kMerge = NW * 16 * kOStride;
     __shared__ __attribute__((aligned(16))) float shared[kTables > kMerge ? kTables : kMerge];
     float* const s_colcs = shared + 8 * D;
     float* const s_blkcs = s_colcs + 32 * kCStride;
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
     uint2 my_rho = make_uint2(0u, 0u);
     {
         const uint16_t* qvec = p.q + (int64_t(b) * p.h_q + hq0 + (head_ok ? r16 : 0)) * D + hf * kHalf;
-        for (int m = wave; m < kM; m += kWaves) {
+        for (int m = wave; m < kM; m += NW) {
             u32x4_t z = {0u, 0u, 0u, 0u};
             if (head_ok) z = *reinterpret_cast<const u32x4_t*>(qvec + 8 * (2 * m + up));
             if constexpr (kRot)
@@ -650,7 +654,7 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
             *reinterpret_cast<u32x4_t*>(&shared[256 * m + 4 * lane]) = z;
         }
         if constexpr (kRot) {
-            for (int e = tid; e < 32 * kHalf; e += kWaves * 64) {
+            for (int e = tid; e < 32 * kHalf; e += NW * 64) {
                 const int cc = e / kHalf, r = e % kHalf;
                 const float u = rope::revolutions(uint32_t(cc), make_uint2(p.rope_rho_hi[r], p.rope_rho_lo[r]));
                 s_colcs[cc * kCStride + 2 * r] = __builtin_amdgcn_cosf(u);
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
     const int tk0 = 16 * (r16 >> 3) + 4 * ((r16 >> 2) & 1) + (r16 & 3);
     const uint32_t v_off = uint32_t(r16 * 32 + hf * 16);
 
-    for (int t0 = t_begin + 32 * wave; t0 < t_end; t0 += 32 * kWaves) {
+    for (int t0 = t_begin + 32 * wave; t0 < t_end; t0 += 32 * NW) {
         const uint16_t* kb = kstream;
         const uint16_t* vb = vblocks;
         int64_t kstride = cap;
@@ -847,7 +851,7 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
     __syncthreads();
     float m_all = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, red_m[w][r16]);
+    for (int w = 0; w < NW; ++w) m_all = fmaxf(m_all, red_m[w][r16]);
     const float f = m_run == -INFINITY ? 0.f : exp2_fast(m_run - m_all);
     if (head_ok) {
 #pragma unroll
@@ -857,20 +861,34 @@ __global__ __launch_bounds__(kWaves * 64, (kRot ? (D == 128 ? 2 : 3) : (D == 128
         }
     }
     __syncthreads();
-    for (int e = tid; e < NH * (D / 4); e += kWaves * 64) {
+    for (int e = tid; e < NH * (D / 4); e += NW * 64) {
         const int h = e / (D / 4), x = 4 * (e % (D / 4));
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, red_m[w][h]);
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, red_m[w][h]);
         f32x4_t o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) o += *reinterpret_cast<const f32x4_t*>(&red_o[(16 * w + h) * kOStride + x]);
+        for (int w = 0; w < NW; ++w) o += *reinterpret_cast<const f32x4_t*>(&red_o[(16 * w + h) * kOStride + x]);
+        float L = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            if (red_m[w][h] != -INFINITY) L += red_l[w][h] * exp2_fast(red_m[w][h] - M);
+        if (p.direct) {
+            // the only split of the row: the output itself
+            const bool empty = !(L > 0.f);  // as in the merge
+            bf16x2_t lo, hi;
+            lo[0] = (__bf16)(empty ? 0.f : o[0] / L);
+            lo[1] = (__bf16)(empty ? 0.f : o[1] / L);
+            hi[0] = (__bf16)(empty ? 0.f : o[2] / L);
+            hi[1] = (__bf16)(empty ? 0.f : o[3] / L);
+            const int64_t row = int64_t(b) * p.h_q + hq0 + h;
+            *reinterpret_cast<uint2*>(p.o + row * D + x) =
+                make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+            if (x == 0) p.lse[row] = empty ? -INFINITY : M * 0.69314718055994531f + logf(L);
+            continue;
+        }
         const int64_t slot = p.n_k_rows != nullptr ? slot0 + h : slot0 + int64_t(h) * p.splits;
         if (x == 0) {
-            float L = 0.f;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w)
-                if (red_m[w][h] != -INFINITY) L += red_l[w][h] * exp2_fast(red_m[w][h] - M);
             p.ws_m[slot] = M;
             p.ws_l[slot] = L;
         }
@@ -957,12 +975,17 @@ hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     const bool ragged = p.n_k_rows != nullptr;
     const dim3 grid(unsigned(ragged ? p.splits + p.batch : p.splits),
                     unsigned(p.h_kv * (p.group / p.heads_per_block)), unsigned(ragged ? 1 : p.batch));
-    // (the 16-column kernel's lane offsets reach over one chunk's stream in 32 bits)
-    if (p.heads_per_block <= 16 && p.cache_tokens < (1 << 27) - 64) {
-        if (p.rotate)
-            hipLaunchKernelGGL((decode_split16_kernel<D, true>), grid, dim3(kWaves * 64), 0, stream, p);
+    if (p.heads_per_block <= 16 && p.cache_tokens < kDecode16MaxTokens) {
+        const dim3 block(unsigned(p.direct ? kDirectWaves : kWaves) * 64);
+        if (p.direct && p.rotate)
+            hipLaunchKernelGGL((decode_split16_kernel<D, true, kDirectWaves>), grid, block, 0, stream, p);
+        else if (p.direct)
+            hipLaunchKernelGGL((decode_split16_kernel<D, false, kDirectWaves>), grid, block, 0, stream, p);
+        else if (p.rotate)
+            hipLaunchKernelGGL((decode_split16_kernel<D, true, kWaves>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((decode_split16_kernel<D, false>), grid, dim3(kWaves * 64), 0, stream, p);
+            hipLaunchKernelGGL((decode_split16_kernel<D, false, kWaves>), grid, block, 0, stream, p);
+        if (p.direct) return hipGetLastError();
     } else if (p.rotate)
         hipLaunchKernelGGL((decode_split_kernel<D, true>), grid, dim3(kWaves * 64), 0, stream, p);
     else

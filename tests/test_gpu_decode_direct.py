@@ -1,0 +1,72 @@
+"""Decode at the edges of the rule that leaves a uniform batch unsplit: a row's keys in one
+workgroup of 8 waves, which writes the output itself, against the split kernels and merge on
+the other side.  Key counts lie at the limits for few and for many rows, at fewer keys than
+waves' groups, and windows end inside the rows; the caches past n_k and the workspace hold
+NaN; pre-rotated and unrotated caches, against the oracle."""
+import math
+
+import pytest
+import torch
+
+from conftest import gpu_available
+import oracle
+import workloads as W
+from parity import compare, note, pack_kcache, pack_vcache, to_f64, windows_for
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+DEV = "cuda"
+
+CASES = [
+    # batch, group, h_kv, n_k, q_pos, d, k
+    (1, 7, 2, 1, 0, 64, 2.0),
+    (3, 3, 8, 225, 224, 128, 2.0),
+    (1, 7, 4, 256, 255, 128, 2.0),      # limits with fewer than 128 workgroups, and past them
+    (1, 7, 4, 257, 256, 128, 2.0),
+    (1, 7, 4, 1280, 1279, 128, 0.5),
+    (1, 7, 4, 1281, 1280, 128, 0.5),
+    (1, 7, 2, 769, 768, 64, math.inf),
+    (1, 7, 2, 2560, 2559, 64, 0.5),
+    (1, 7, 2, 2561, 2560, 64, 0.5),
+    (1, 7, 2, 9000, 2559, 64, 0.5),     # the limit counts keys up to the query
+    (64, 2, 2, 769, 768, 128, 2.0),     # 128 workgroups
+    (127, 1, 2, 1025, 1030, 64, 2.0),   # 254, the query past the cache's end
+    (64, 16, 4, 513, 512, 64, 2.0),     # 256 workgroups, whole tiles of heads
+    (32, 3, 8, 1600, 1599, 128, 0.5),
+]
+
+
+@pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(x) for x in c))
+def test_decode_direct(case, unrotated):
+    import paper_2608_02947_amd as atf
+    B, G, h_kv, n_k, q_pos, d, kwin = case
+    h_q, cap, base = G * h_kv, n_k + 21, 1e4
+    g = torch.Generator(device="cpu").manual_seed(B * 1009 + n_k)
+    q = torch.randn((B, 1, h_q, d), generator=g).to(torch.bfloat16)
+    k = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    v = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    th = W.rope_theta(d, base)
+    win, widths = windows_for(d, base, kwin, None, n_ctx=max(n_k, q_pos + 1))
+    qr = W.rotate_half(q, torch.tensor([q_pos]), th)
+    kr = W.rotate_half(k, torch.arange(n_k), th)
+    rows = torch.tensor([0, B // 2, B - 1]).unique()  # of a large batch three rows are compared
+    o_ref, lse_ref, _ = oracle.attend(qr[rows], kr[rows], v[rows], q_pos, widths)
+
+    def cache(x, pack):
+        full = torch.full((B, cap, h_kv, d), float("nan"), dtype=torch.bfloat16)
+        full[:, :n_k] = x
+        return pack(full.to(DEV))
+
+    kp, vp = cache(k if unrotated else kr, pack_kcache), cache(v, pack_vcache)
+    qd = (q if unrotated else qr)[:, 0].contiguous().to(DEV)
+    ws = torch.full((atf.atf_decode_workspace_bytes(B, h_q, h_kv, n_k, d),), 255, dtype=torch.uint8, device=DEV)
+    o = torch.full_like(qd, float("nan"))
+    lse = torch.full((B, h_q), float("nan"), dtype=torch.float32, device=DEV)
+    note(f"decode direct {case} unrotated={unrotated}")
+    fn = atf.atf_decode_unrotated if unrotated else atf.atf_decode
+    fn(qd, kp, vp, o, lse, q_pos, win, ws, n_k=n_k)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
+    compare(to_f64(o[rows.to(DEV)]), to_f64(lse[rows.to(DEV)]), o_ref[:, 0], lse_ref[:, :, 0], f"direct {case}")

@@ -208,7 +208,7 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
     return static_cast<int32_t>(std::max<int64_t>(1, (steps + per - 1) / per));
 }
 
-// Whether a uniform batch takes one workgroup of 8 waves per (row, KV head), which writes the
+// Whether a batch takes one workgroup of 8 waves per (row, KV head), which writes the
 // output itself, and no merge.
 //
 // With 256 such workgroups or more every CU has one, and splitting only adds the partial
@@ -221,12 +221,22 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // d = 128 12.3 -> 11.5 at 1,280, 12.4 -> 12.3 at 1,600; d = 64 13.4 -> 10.8 at 2,048,
 // 13.2 -> 11.2 at 2,560, 13.6 -> 13.7 at 3,000; rotating d = 128 12.1 -> 10.5 at 256,
 // 12.0 -> 13.6 at 512, d = 64 13.5 -> 11.8 at 768, 13.3 -> 13.4 at 1,000.
+//
+// Of a ragged batch only the longest row's bound is known here, and one long row among short
+// ones is then one workgroup's work: below 1,024 workgroups the limit is the last of these (8
+// to 128 rows up to 300 keys, 24/8 heads 15.2..42.5 -> 11.2..23.1; up to 1,280 14.9 -> 12.4; 64
+// rows of d = 64 up to 3,840 18.3 -> 22.0).  From 1,024 the plan and merge of all rows cost
+// more than a long row does: 128 rows up to 1,920 73.9 -> 60.3 (but one row of 3,840 keys
+// among 127 of one key 39.7 -> 46.2); 512 rows of d = 64 up to 300 keys 54.2 -> 12.1, up to
+// 7,680 148.9 -> 131.0, one row of 7,680 among rows of one key 55.5 -> 28.6.
 bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
-                   int32_t heads_per_block, bool rotate) {
+                   int32_t heads_per_block, bool rotate, bool ragged) {
     if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
-    if (cols >= 256) return true;
-    if (cols >= 128) return n_valid <= (rotate ? (head_dim == 64 ? 1024 : 768) : (head_dim == 64 ? 7680 : 3840));
+    if (!ragged && cols >= 256) return true;
+    if (cols >= (ragged ? 1024 : 128))
+        return n_valid <= (rotate ? (head_dim == 64 ? 1024 : 768)
+                                  : head_dim == 64 ? 7680 : ragged ? 2560 : 3840);
     return n_valid <= (rotate ? (head_dim == 64 ? 768 : 256) : (head_dim == 64 ? 2560 : 1280));
 }
 
@@ -751,10 +761,11 @@ int decode_impl(const char* fn, const void* q, const void* k_cache, const void* 
         p.n_valid = static_cast<int32_t>(n_k);
         p.splits = atf::decode_plan_items(h_kv * (group / hpb), hpb);
         p.split_tokens = 0;
+        p.direct = atf::decode_direct(batch, h_q, d, n_k, cache_tokens, hpb, rope.rotate, true);
     } else {
         const int64_t last = q_pos < n_k - 1 ? q_pos : n_k - 1;
         p.n_valid = static_cast<int32_t>(last + 1);
-        const bool direct = atf::decode_direct(batch, h_q, d, p.n_valid, cache_tokens, hpb, rope.rotate);
+        const bool direct = atf::decode_direct(batch, h_q, d, p.n_valid, cache_tokens, hpb, rope.rotate, false);
         const int32_t splits =
             direct ? 1 : atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, rope.rotate);
         p.splits = splits;

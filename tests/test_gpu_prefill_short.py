@@ -90,3 +90,33 @@ def test_few_rows_and_many_rows(case, unrotated):
     diff = (o1.double() - o2[:1].double()).abs()
     assert float((diff - 2.0 ** -7 * torch.maximum(o1.double().abs(), o2[:1].double().abs())).max()) <= 1e-2
     assert np.abs(to_f64(l1) - to_f64(l2[:1])).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what", ["query", "keys"])
+def test_nan_reaches_the_lse(what, d):
+    """A row whose scores are NaN, in every wave (its query is NaN) or in one wave only (a
+    32-key block is), has a NaN output and LSE with few rows as with many; keys end before
+    every query at a whole block, so that no mask touches a score."""
+    import paper_2608_02947_amd as atf
+    n_q, n_k, q0 = 9, 128, 200
+    g = torch.Generator(device="cpu").manual_seed(d)
+    q = torch.randn((1, n_q, 2, d), generator=g).to(torch.bfloat16)
+    k, v = (torch.randn((1, n_k, 1, d), generator=g).to(torch.bfloat16) for _ in range(2))
+    if what == "query":
+        q[0, 4, 1] = math.nan
+        bad = torch.zeros((2, n_q), dtype=torch.bool)
+        bad[1, 4] = True
+    else:
+        k[0, 32:64] = math.nan
+        bad = torch.ones((2, n_q), dtype=torch.bool)
+    for kwin in (2.0, math.inf):
+        win, _ = windows_for(d, 1e6, kwin, None, n_ctx=q0 + n_q)
+        for B in (1, 400):
+            rep = lambda x: x.expand(B, *x.shape[1:]).contiguous()
+            note(f"nan {what} d={d} k={kwin} B={B}")
+            o, lse = _run(atf.atf_prefill, rep(q.to(DEV)), rep(pack_kcache(k.to(DEV))),
+                          rep(pack_vcache(v.to(DEV))), q0, win, n_k)
+            for b in {0, B - 1}:
+                assert torch.equal(lse[b].isnan().cpu(), bad), (kwin, B)
+                assert torch.equal(o[b].isnan().cpu(), bad.T[:, :, None].expand(n_q, 2, d)), (kwin, B)

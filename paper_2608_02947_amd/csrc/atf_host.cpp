@@ -186,6 +186,12 @@ int32_t decode_ragged_items(int32_t cols) {
     return static_cast<int32_t>(s);
 }
 
+namespace {
+// rounds of the chip's CUs that a number of equal workgroups takes
+constexpr int64_t kDecodeCUs = 256;
+int64_t decode_rounds(int64_t groups) { return (groups + kDecodeCUs - 1) / kDecodeCUs; }
+}  // namespace
+
 // Splits a uniform batch uses, at most the decode_splits() its workspace has room for.
 //
 // Up to 16 heads per workgroup: as many workgroups as the CUs hold at once, 3 of
@@ -193,16 +199,26 @@ int32_t decode_ragged_items(int32_t cols) {
 // made anew by every workgroup), so that the batch runs in one round of equal splits:
 // 2^20 keys, 28/4 heads 283 us with 1024, 273 with 768; batch 8 at 32,768 keys, 24/8 heads
 // 156 -> 153; rotating, batch 2 at 100,003 keys 65.9 -> 63.5, batch 8 at 8,200 36.1 -> 30.7
-// (512; 31.6 with 768).  More heads: 1024, two rounds of the 2 workgroups per CU of
-// decode_split_kernel (2048 is 6 % slower at 2^20 keys).  The steps are then spread evenly:
-// 65 steps over 12 splits are 11 splits of 6, not 10 of 6 and one of 5 beside an empty one.
+// (512; 31.6 with 768).  From 256 (row, KV head) pairs on: the splits that leave the fewest
+// rounds of 256, counted in whole rows (decode_direct).  More heads: 1024, two rounds of the
+// 2 workgroups per CU of decode_split_kernel (2048 is 6 % slower at 2^20 keys).  The steps
+// are then spread evenly: 65 steps over 12 splits are 11 splits, ten of 6 and one of 5, not
+// 10 of 6, one of 5 and an empty one.
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
                            int32_t heads_per_block, bool rotate) {
     const int64_t room = decode_splits(batch, h_kv, n_k);
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
-    const int64_t target = heads_per_block > 16 ? 1024 : rotate ? 512 : 768;
+    const int64_t target = rotate ? 512 : 768;
     const int64_t steps = (n_valid + kDecodeTokenStep - 1) / kDecodeTokenStep;
-    int64_t s = heads_per_block > 16 ? room : std::min(room, std::max<int64_t>(1, target / cols));
+    int64_t s = 1;
+    if (heads_per_block > 16) {
+        s = room;
+    } else if (cols < kDecodeCUs) {
+        s = std::min(room, std::max<int64_t>(1, target / cols));
+    } else {
+        for (int64_t t = 2; t <= std::min<int64_t>(room, 4); ++t)
+            if (decode_rounds(t * cols) * s < decode_rounds(s * cols) * t) s = t;
+    }
     s = std::max<int64_t>(1, std::min(s, steps));
     const int64_t per = (steps + s - 1) / s;
     return static_cast<int32_t>(std::max<int64_t>(1, (steps + per - 1) / per));
@@ -211,9 +227,25 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // Whether a batch takes one workgroup of 8 waves per (row, KV head), which writes the
 // output itself, and no merge.
 //
-// With 256 such workgroups or more every CU has one, and splitting only adds the partial
-// states' way through memory and the merge (us, split -> direct): 32 rows of 500 keys, 24/8
-// heads 19.8 -> 14.0, of 16,000 306 -> 295; rotating 23.9 -> 18.3, and 173 -> 155 at 8,000.
+// With 256 such workgroups every CU has one, and splitting only adds the partial states' way
+// through memory and the merge (us, split -> direct): 32 rows of 500 keys, 24/8 heads
+// 19.8 -> 14.0, of 16,000 306 -> 295; rotating 23.9 -> 18.3, and 173 -> 155 at 8,000.
+// Just past a whole round of the CUs some of them take a row more while the others wait, and a
+// split plan has smaller pieces to deal out: 24/8 heads, 16,000 keys, 33 rows 310 -> 382, 40
+// rows 351 -> 398, 44 rows 389 -> 409, 48 rows 409 -> 405, 66 rows 615 -> 654, 76 rows
+// 643 -> 646; rotating, 33 rows 342 -> 440, 42 rows 385 -> 452, 44 rows 433 -> 453, 66 rows
+// 686 -> 713; d = 64, 16/16 heads, 17 rows 174 -> 213, rotating 184 -> 257, 24 rows 241 -> 265,
+// 40 rows 380 -> 401 (at 4,000 keys 110 -> 130).  So they are split in a second or third round
+// of up to 85 (rotating at d = 64 128) workgroups; a fourth gains at most 4 %, and from 1,025
+// pairs on the workspace has room for one split only.  A row has to be long enough to pay for
+// the merge, which grows with its heads: 264 pairs of 3 heads, 1,000 keys 33.2 -> 34.7, 2,000
+// 53.4 -> 60.8; of 7, 2,000 59.4 -> 60.1, 8,000 179 -> 204; of 16, 4,000 112 -> 110, 8,000
+// 193 -> 206; in the third round, 528 pairs of 7 heads without a window, 16,000 772 -> 817.
+// Rotating at d = 64, a CU holds 8 waves of the unsplit kernel and 12 of the split one: with 1
+// or 2 heads, whose merge costs least, the latter wins from 1,025 pairs on (2,112 pairs of 1
+// head, 300 keys 50 -> 62, 4,000 353 -> 378, 16,000 1242 -> 1261; of 2, 1,000 keys 110 -> 118,
+// but 1,056 pairs 66.1 -> 65.6; of 7, 137 -> 120).
+//
 // With 128 to 255 they win while a row is short: d = 128 39.3 -> 33.8 at 3,840 keys,
 // 62.3 -> 68.9 at 5,000 without a window; d = 64 39.5 -> 34.1 at 7,680, 60.4 -> 66.8 at 10,000;
 // rotating d = 128 18.8 -> 18.7 at 768, 21.2 -> 21.4 at 1,024, d = 64 14.2 -> 14.0 at 1,024,
@@ -233,7 +265,13 @@ bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid
                    int32_t heads_per_block, bool rotate, bool ragged) {
     if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
-    if (!ragged && cols >= 256) return true;
+    if (!ragged && cols >= kDecodeCUs) {
+        const int64_t rounds = decode_rounds(cols), last = cols - (rounds - 1) * kDecodeCUs;
+        if (rounds > 4) return !(rotate && head_dim == 64 && heads_per_block <= 2);
+        if (rounds == 1 || rounds == 4 || last > (rotate && head_dim == 64 ? 128 : 85)) return true;
+        const int64_t keys = (rotate ? 192 : head_dim == 64 ? 512 : 320) * (rounds == 2 ? 1 : 4);
+        return n_valid < std::max<int64_t>(rotate ? 1024 : 2048, keys * heads_per_block * (64 + last) / 64);
+    }
     if (cols >= (ragged ? 1024 : 128))
         return n_valid <= (rotate ? (head_dim == 64 ? 1024 : 768)
                                   : head_dim == 64 ? 7680 : ragged ? 2560 : 3840);

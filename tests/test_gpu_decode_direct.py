@@ -10,6 +10,7 @@ import torch
 
 from conftest import gpu_available
 import oracle
+import routes
 import workloads as W
 from parity import compare, note, pack_kcache, pack_vcache, to_f64, windows_for
 
@@ -70,6 +71,61 @@ def test_decode_direct(case, unrotated):
     torch.cuda.synchronize()
     assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
     compare(to_f64(o[rows.to(DEV)]), to_f64(lse[rows.to(DEV)]), o_ref[:, 0], lse_ref[:, :, 0], f"direct {case}")
+
+
+# just past whole rounds of 256 workgroups, where long rows are split after all
+ROUNDS = [
+    # batch, group, h_kv, n_k, d, splits pre-rotated, splits unrotated (0: direct)
+    (33, 3, 8, 2100, 128, 4, 4),
+    (33, 3, 8, 2040, 128, 0, 4),     # too short, pre-rotated
+    (42, 2, 8, 2049, 128, 3, 3),
+    (44, 1, 8, 4000, 128, 0, 0),     # 352: nearer two rounds
+    (66, 1, 8, 3100, 128, 2, 2),     # 528
+    (17, 1, 16, 2100, 64, 4, 4),
+    (24, 1, 16, 1200, 64, 0, 2),     # 384
+    (65, 1, 16, 300, 64, 0, 1),      # 1,040: no room for two splits
+    (130, 2, 8, 129, 64, 0, 1),
+]
+
+
+@pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])
+@pytest.mark.parametrize("case", ROUNDS, ids=lambda c: "x".join(str(x) for x in c))
+def test_decode_between_whole_rounds(case, unrotated):
+    """Three different rows, each in a third of the batch: all copies of a row agree bit for
+    bit, and the rows agree with the oracle."""
+    import paper_2608_02947_amd as atf
+    B, G, h_kv, n_k, d, *splits = case
+    h_q, base, q_pos, cap = G * h_kv, 1e4, n_k - 1, n_k + 21
+    direct = routes.decode_direct(B, G, h_kv, n_k, q_pos, d, unrotated, cap=cap)
+    plan = 0 if direct else routes.decode_splits(B, G, h_kv, n_k, q_pos, unrotated)[0]
+    assert plan == splits[unrotated]
+    g = torch.Generator(device="cpu").manual_seed(B * 1009 + n_k)
+    q = torch.randn((3, 1, h_q, d), generator=g).to(torch.bfloat16)
+    k = torch.randn((3, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    v = torch.randn((3, n_k, h_kv, d), generator=g).to(torch.bfloat16)
+    th = W.rope_theta(d, base)
+    win, widths = windows_for(d, base, 2.0, None, n_ctx=n_k)
+    qr = W.rotate_half(q, torch.tensor([q_pos]), th)
+    kr = W.rotate_half(k, torch.arange(n_k), th)
+    o_ref, lse_ref, _ = oracle.attend(qr, kr, v, q_pos, widths)
+    row = torch.arange(B, device=DEV) % 3
+
+    def cache(x, pack):
+        full = torch.full((3, cap, h_kv, d), float("nan"), dtype=torch.bfloat16)
+        full[:, :n_k] = x
+        return pack(full.to(DEV))[row]
+
+    kp, vp = cache(k if unrotated else kr, pack_kcache), cache(v, pack_vcache)
+    qd = (q if unrotated else qr)[:, 0].to(DEV)[row]
+    ws = torch.full((atf.atf_decode_workspace_bytes(B, h_q, h_kv, n_k, d),), 255, dtype=torch.uint8, device=DEV)
+    o = torch.full_like(qd, float("nan"))
+    lse = torch.full((B, h_q), float("nan"), dtype=torch.float32, device=DEV)
+    note(f"decode rounds {case} unrotated={unrotated}")
+    fn = atf.atf_decode_unrotated if unrotated else atf.atf_decode
+    fn(qd, kp, vp, o, lse, q_pos, win, ws, n_k=n_k)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o[:3][row]) and torch.equal(lse, lse[:3][row])
+    compare(to_f64(o[:3]), to_f64(lse[:3]), o_ref[:, 0], lse_ref[:, :, 0], f"rounds {case}")
 
 
 # a ragged batch's bound on its rows' keys: at the limits for few and for many workgroups

@@ -232,15 +232,17 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // 19.8 -> 14.0, of 16,000 306 -> 295; rotating 23.9 -> 18.3, and 173 -> 155 at 8,000.
 // Just past a whole round of the CUs some of them take a row more while the others wait, and a
 // split plan has smaller pieces to deal out: 24/8 heads, 16,000 keys, 33 rows 310 -> 382, 40
-// rows 351 -> 398, 44 rows 389 -> 409, 48 rows 409 -> 405, 66 rows 615 -> 654, 76 rows
-// 643 -> 646; rotating, 33 rows 342 -> 440, 42 rows 385 -> 452, 44 rows 433 -> 453, 66 rows
-// 686 -> 713; d = 64, 16/16 heads, 17 rows 174 -> 213, rotating 184 -> 257, 24 rows 241 -> 265,
-// 40 rows 380 -> 401 (at 4,000 keys 110 -> 130).  So they are split in a second or third round
-// of up to 85 (rotating at d = 64 128) workgroups; a fourth gains at most 4 %, and from 1,025
-// pairs on the workspace has room for one split only.  A row has to be long enough to pay for
-// the merge, which grows with its heads: 264 pairs of 3 heads, 1,000 keys 33.2 -> 34.7, 2,000
-// 53.4 -> 60.8; of 7, 2,000 59.4 -> 60.1, 8,000 179 -> 204; of 16, 4,000 112 -> 110, 8,000
-// 193 -> 206; in the third round, 528 pairs of 7 heads without a window, 16,000 772 -> 817.
+// rows 351 -> 398, 48 rows 409 -> 405, 52 rows 448 -> 423, 66 rows 615 -> 654, 76 rows
+// 643 -> 646; 98 rows of 60,000 keys 3018 -> 3145; rotating, 16,000 keys, 33 rows 342 -> 440, 42 rows 385 -> 452, 66
+// rows 686 -> 713; d = 64, 16/16 heads, 17 rows 174 -> 213, rotating 184 -> 257, 24 rows
+// 241 -> 265, 40 rows 380 -> 401.  So they are split in a second to fourth round of up to 128
+// workgroups (from 1,025 pairs on the workspace has room for one split only), if a row is long
+// enough to pay for the merge, which grows with its heads, out of what the round leaves idle,
+// which falls with the round's workgroups and with the rounds before it: the limit is a fit
+// to 1,400 measured calls of 257 to 1,023 pairs, 1 to 16 heads and 300 to 60,000 keys.  264
+// pairs of 3 heads, 1,000 keys 33.2 -> 34.7, 2,000 53.4 -> 60.8; of 7, 2,000 59.4 -> 60.1, 8,000
+// 179 -> 204; of 16, 4,000 112 -> 110, 8,000 193 -> 206; 528 pairs of 7 heads without a window,
+// 8,000 keys 404 -> 415, 60,000 2800 -> 3017.
 // Rotating at d = 64, a CU holds 8 waves of the unsplit kernel and 12 of the split one: with 1
 // or 2 heads, whose merge costs least, the latter wins from 1,025 pairs on (2,112 pairs of 1
 // head, 300 keys 50 -> 62, 4,000 353 -> 378, 16,000 1242 -> 1261; of 2, 1,000 keys 110 -> 118,
@@ -268,9 +270,10 @@ bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid
     if (!ragged && cols >= kDecodeCUs) {
         const int64_t rounds = decode_rounds(cols), last = cols - (rounds - 1) * kDecodeCUs;
         if (rounds > 4) return !(rotate && head_dim == 64 && heads_per_block <= 2);
-        if (rounds == 1 || rounds == 4 || last > (rotate && head_dim == 64 ? 128 : 85)) return true;
-        const int64_t keys = (rotate ? 192 : head_dim == 64 ? 512 : 320) * (rounds == 2 ? 1 : 4);
-        return n_valid < std::max<int64_t>(rotate ? 1024 : 2048, keys * heads_per_block * (64 + last) / 64);
+        if (rounds == 1 || last > 128) return true;
+        const double keys = (rotate ? 128 : head_dim == 64 ? 512 : 256) * (rounds == 2 ? 1 : 4);
+        return n_valid < std::max(!rotate && head_dim == 64 ? 2048.0 : 1024.0,
+                                  keys * heads_per_block * std::exp2(double(last) / 48));
     }
     if (cols >= (ragged ? 1024 : 128))
         return n_valid <= (rotate ? (head_dim == 64 ? 1024 : 768)

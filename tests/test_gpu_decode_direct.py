@@ -76,13 +76,15 @@ def test_decode_direct(case, unrotated):
 # just past whole rounds of 256 workgroups, where long rows are split after all
 ROUNDS = [
     # batch, group, h_kv, n_k, d, splits pre-rotated, splits unrotated (0: direct)
+    (33, 3, 8, 1000, 128, 0, 0),     # too short for either
     (33, 3, 8, 2100, 128, 4, 4),
-    (33, 3, 8, 2040, 128, 0, 4),     # too short, pre-rotated
     (42, 2, 8, 2049, 128, 3, 3),
-    (44, 1, 8, 4000, 128, 0, 0),     # 352: nearer two rounds
+    (44, 1, 8, 4000, 128, 2, 2),     # 352 pairs
+    (50, 1, 8, 4000, 128, 0, 0),     # 400: nearer two rounds
     (66, 1, 8, 3100, 128, 2, 2),     # 528
+    (100, 1, 8, 2000, 128, 2, 2),    # 800
     (17, 1, 16, 2100, 64, 4, 4),
-    (24, 1, 16, 1200, 64, 0, 2),     # 384
+    (24, 1, 16, 1200, 64, 0, 2),     # 384, too short pre-rotated
     (65, 1, 16, 300, 64, 0, 1),      # 1,040: no room for two splits
     (130, 2, 8, 129, 64, 0, 1),
 ]

@@ -9,9 +9,9 @@ import routes
 @pytest.mark.parametrize("batch,group,h_kv,n_k,d,rotate,splits", [
     # (row, KV head) pairs: exactly a round of 256 CUs, just past it, nearly two
     (32, 3, 8, 16000, 128, False, 0), (33, 3, 8, 16000, 128, False, 4), (40, 3, 8, 16000, 128, False, 4),
-    (42, 3, 8, 16000, 128, False, 3), (48, 3, 8, 16000, 128, False, 0), (64, 3, 8, 16000, 128, False, 0),
+    (42, 3, 8, 16000, 128, False, 3), (52, 3, 8, 16000, 128, False, 0), (64, 3, 8, 16000, 128, False, 0),
     (33, 3, 8, 16000, 128, True, 4), (42, 3, 8, 4000, 128, True, 3), (56, 3, 8, 4000, 128, True, 0),
-    (66, 3, 8, 16000, 128, False, 2), (88, 3, 8, 16000, 128, False, 0),
+    (66, 3, 8, 16000, 128, False, 2), (88, 3, 8, 16000, 128, False, 0), (100, 3, 8, 60000, 128, False, 2),
     # rows too short to pay for the merge, the more so with many heads
     (33, 3, 8, 1000, 128, False, 0), (66, 16, 4, 4000, 128, False, 0), (66, 16, 4, 8000, 128, False, 4),
     (66, 3, 8, 2000, 128, False, 0),

@@ -192,7 +192,28 @@ constexpr int64_t kDecodeCUs = 256;
 int64_t decode_rounds(int64_t groups) { return (groups + kDecodeCUs - 1) / kDecodeCUs; }
 }  // namespace
 
+// Whether a call's workgroups take decode_split16_kernel: up to 16 heads each, and caches within
+// its lane offsets (they reach over one chunk's stream).
+//
+// Not where several workgroups share a KV head (35, 39 or 49 heads to one: 7 by 5, 13 by 3, 7 by
+// 7), keys are not rotated and the batch's caches pass the 256 MB last-level cache: more
+// workgroups are then in flight at places further apart, and keys that one has read have left
+// the caches when the next one of the same KV head comes (split16 against
+// decode_split_kernel: 146 rows of 86,558 keys, 70/2 heads 4813 and 3385 us, 270 rows of 40,029,
+// 39/1 1879 and 1607; but 21 rows of 6,824, 70/2, and smaller ones 0.3 to 1.0 of the time).
+bool decode_cols16(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
+                   int64_t cache_tokens, int32_t heads_per_block, bool rotate) {
+    if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
+    return rotate || h_q / h_kv == heads_per_block ||
+           int64_t(batch) * h_kv * n_valid <= (int64_t(256) << 20) / (4 * head_dim);
+}
+
 // Splits a uniform batch uses, at most the decode_splits() its workspace has room for.
+//
+// Where several workgroups share a KV head (64 heads to one: two of 32), all of them: the
+// workgroups that read the same keys are that many apart and, where it is a multiple of 8, on
+// the same XCD (16 rows of 123,544 keys, 64/1 heads: 64 splits, 3 of them empty, 201 us, the
+// other 61 by themselves 235).
 //
 // Up to 16 heads per workgroup: as many workgroups as the CUs hold at once, 3 of
 // decode_split16_kernel (768) or 2 where it rotates keys (512, at d = 128; its tables are
@@ -205,13 +226,14 @@ int64_t decode_rounds(int64_t groups) { return (groups + kDecodeCUs - 1) / kDeco
 // are then spread evenly: 65 steps over 12 splits are 11 splits, ten of 6 and one of 5, not
 // 10 of 6, one of 5 and an empty one.
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
-                           int32_t heads_per_block, bool rotate) {
+                           int32_t heads_per_block, bool cols16, bool rotate) {
     const int64_t room = decode_splits(batch, h_kv, n_k);
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
     const int64_t target = rotate ? 512 : 768;
     const int64_t steps = (n_valid + kDecodeTokenStep - 1) / kDecodeTokenStep;
+    if (h_q / h_kv != heads_per_block) return static_cast<int32_t>(room);
     int64_t s = 1;
-    if (heads_per_block > 16) {
+    if (!cols16) {
         s = room;
     } else if (cols < kDecodeCUs) {
         s = std::min(room, std::max<int64_t>(1, target / cols));
@@ -243,6 +265,9 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // pairs of 3 heads, 1,000 keys 33.2 -> 34.7, 2,000 53.4 -> 60.8; of 7, 2,000 59.4 -> 60.1, 8,000
 // 179 -> 204; of 16, 4,000 112 -> 110, 8,000 193 -> 206; 528 pairs of 7 heads without a window,
 // 8,000 keys 404 -> 415, 60,000 2800 -> 3017.
+// Where several workgroups share a KV head, only short rows run unsplit: those workgroups are
+// up to a round of the chip apart, and the second one finds the keys gone from the caches (270
+// rows of 40,029 keys, 39/1 heads 1615 -> 2926; rotating, 281 rows of 7,939, 70/2 1506 -> 1854).
 // Rotating at d = 64, a CU holds 8 waves of the unsplit kernel and 12 of the split one: with 1
 // or 2 heads, whose merge costs least, the latter wins from 1,025 pairs on (2,112 pairs of 1
 // head, 300 keys 50 -> 62, 4,000 353 -> 378, 16,000 1242 -> 1261; of 2, 1,000 keys 110 -> 118,
@@ -263,11 +288,10 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // more than a long row does: 128 rows up to 1,920 73.9 -> 60.3 (but one row of 3,840 keys
 // among 127 of one key 39.7 -> 46.2); 512 rows of d = 64 up to 300 keys 54.2 -> 12.1, up to
 // 7,680 148.9 -> 131.0, one row of 7,680 among rows of one key 55.5 -> 28.6.
-bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
+bool decode_direct(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
                    int32_t heads_per_block, bool rotate, bool ragged) {
-    if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
-    if (!ragged && cols >= kDecodeCUs) {
+    if (!ragged && cols >= kDecodeCUs && h_q / h_kv == heads_per_block) {
         const int64_t rounds = decode_rounds(cols), last = cols - (rounds - 1) * kDecodeCUs;
         if (rounds > 4) return !(rotate && head_dim == 64 && heads_per_block <= 2);
         if (rounds == 1 || last > 128) return true;
@@ -288,9 +312,9 @@ bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid
 // 219 -> 214 us (24/8 heads), 124 -> 120 (28/4); 4 rows up to 60K 65 -> 63, 38 -> 36; 24
 // rows up to 30K 159 -> 161, 94 -> 92.  decode_split_kernel keeps 2048 (5-12 % faster than
 // 1024, up to 20 % than 4096).
-int32_t decode_plan_items(int32_t cols, int32_t heads_per_block) {
+int32_t decode_plan_items(int32_t cols, bool cols16) {
     const int32_t room = decode_ragged_items(cols);
-    return heads_per_block > 16 ? room : std::min(room, std::max(1, 1536 / cols));
+    return cols16 ? std::min(room, std::max(1, 1536 / cols)) : room;
 }
 
 }  // namespace atf
@@ -795,20 +819,19 @@ int decode_impl(const char* fn, const void* q, const void* k_cache, const void* 
     p.max_pages = pg.max_pages;
     p.num_pages = pg.num_pages;
     p.page_tokens = pg.page_tokens;
+    p.n_valid = static_cast<int32_t>(ragged ? n_k : std::min(q_pos, n_k - 1) + 1);
+    p.cols16 = atf::decode_cols16(batch, h_q, h_kv, d, p.n_valid, cache_tokens, hpb, rope.rotate);
     if (ragged) {
         // the work items are laid out on the device from the row arrays: the batch's
         // keys in about `splits` equal spans (multiples of the workgroup's token step)
         // per column, each row cut into whole spans of its own keys
-        p.n_valid = static_cast<int32_t>(n_k);
-        p.splits = atf::decode_plan_items(h_kv * (group / hpb), hpb);
+        p.splits = atf::decode_plan_items(h_kv * (group / hpb), p.cols16);
         p.split_tokens = 0;
-        p.direct = atf::decode_direct(batch, h_q, d, n_k, cache_tokens, hpb, rope.rotate, true);
+        p.direct = p.cols16 && atf::decode_direct(batch, h_q, h_kv, d, n_k, hpb, rope.rotate, true);
     } else {
-        const int64_t last = q_pos < n_k - 1 ? q_pos : n_k - 1;
-        p.n_valid = static_cast<int32_t>(last + 1);
-        const bool direct = atf::decode_direct(batch, h_q, d, p.n_valid, cache_tokens, hpb, rope.rotate, false);
+        const bool direct = p.cols16 && atf::decode_direct(batch, h_q, h_kv, d, p.n_valid, hpb, rope.rotate, false);
         const int32_t splits =
-            direct ? 1 : atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, rope.rotate);
+            direct ? 1 : atf::decode_plan_splits(batch, h_q, h_kv, n_k, p.n_valid, hpb, p.cols16, rope.rotate);
         p.splits = splits;
         p.direct = direct;
         const auto step_of = [&](int64_t s) {

@@ -77,6 +77,7 @@ struct DecodeParams {
     // at position pos is rotated by pos * theta_r, with rho_r = theta_r / (2 pi) mod 1
     // as a 0.64 fixed-point fraction (hi and lo words)
     int32_t rotate;
+    int32_t cols16;           // decode_split16_kernel, not decode_split_kernel
     int32_t direct;           // one split per row, which writes the output itself (no merge)
     uint32_t rope_rho_hi[kMaxPairs];
     uint32_t rope_rho_lo[kMaxPairs];
@@ -121,12 +122,14 @@ hipError_t launch_rotate_kcache(const RotateParams& p, int head_dim, hipStream_t
 // `cols` = kv heads x head subgroups of a ragged one: what the workspace has room for.
 int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k);
 int32_t decode_ragged_items(int32_t cols);
-// The numbers a call uses.
+// The kernel and the numbers a call uses; n_valid bounds a ragged batch's rows.
+bool decode_cols16(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
+                   int64_t cache_tokens, int32_t heads_per_block, bool rotate);
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
-                           int32_t heads_per_block, bool rotate);
-int32_t decode_plan_items(int32_t cols, int32_t heads_per_block);
-// Whether a batch runs without splits; n_valid bounds a ragged one's rows.
-bool decode_direct(int32_t batch, int32_t h_q, int32_t head_dim, int64_t n_valid, int64_t cache_tokens,
+                           int32_t heads_per_block, bool cols16, bool rotate);
+int32_t decode_plan_items(int32_t cols, bool cols16);
+// Whether a batch runs without splits (with cols16 only).
+bool decode_direct(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
                    int32_t heads_per_block, bool rotate, bool ragged);
 // Caches from this many tokens are out of the 32-bit lane offsets of decode_split16_kernel
 // (they reach over one chunk's stream) and take decode_split_kernel.

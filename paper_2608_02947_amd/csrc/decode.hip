@@ -985,7 +985,7 @@ hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
     const dim3 grid(unsigned(p.direct ? p.batch : ragged ? p.splits + p.batch : p.splits),
                     unsigned(p.h_kv * (p.group / p.heads_per_block)),
                     unsigned(p.direct || ragged ? 1 : p.batch));
-    if (p.heads_per_block <= 16 && p.cache_tokens < kDecode16MaxTokens) {
+    if (p.cols16) {
         const dim3 block(unsigned(p.direct ? kDirectWaves : kWaves) * 64);
         if (p.direct && p.rotate)
             hipLaunchKernelGGL((decode_split16_kernel<D, true, kDirectWaves>), grid, block, 0, stream, p);
@@ -1012,7 +1012,8 @@ hipError_t launch_decode_d(const DecodeParams& p, hipStream_t stream) {
 hipError_t launch_decode(const DecodeParams& p, int head_dim, hipStream_t stream) {
     if (p.splits < 1 || p.splits > kDecodeMaxSplits) return hipErrorInvalidValue;
     if (p.heads_per_block < 1 || p.heads_per_block > kDecodeMaxHeads ||
-        p.group % p.heads_per_block != 0)
+        p.group % p.heads_per_block != 0 ||
+        (p.cols16 ? p.heads_per_block > 16 || p.cache_tokens >= kDecode16MaxTokens : p.direct))
         return hipErrorInvalidValue;
     if (p.n_k_rows == nullptr &&
         (int64_t(p.splits) * p.split_tokens < p.n_valid || p.split_tokens % kDecodeTokenStep != 0))

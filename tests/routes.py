@@ -16,8 +16,9 @@ def _rule(name, restype, *argtypes):
     return f
 
 
-_direct = _rule("_ZN3atf13decode_directEiiillibb", _bool, _i32, _i32, _i32, _i64, _i64, _i32, _bool, _bool)
-_plan = _rule("_ZN3atf18decode_plan_splitsEiiillib", _i32, _i32, _i32, _i32, _i64, _i64, _i32, _bool)
+_direct = _rule("_ZN3atf13decode_directEiiiilibb", _bool, _i32, _i32, _i32, _i32, _i64, _i32, _bool, _bool)
+_cols16 = _rule("_ZN3atf13decode_cols16Eiiiillib", _bool, _i32, _i32, _i32, _i32, _i64, _i64, _i32, _bool)
+_plan = _rule("_ZN3atf18decode_plan_splitsEiiillibb", _i32, _i32, _i32, _i32, _i64, _i64, _i32, _bool, _bool)
 _room = _rule("_ZN3atf13decode_splitsEiil", _i32, _i32, _i32, _i64)
 
 
@@ -26,13 +27,21 @@ def heads_per_block(group):
     return max(c for c in range(1, 33) if group % c == 0)
 
 
+def decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate=False, ragged=False, cap=None):
+    """Whether the heads are the columns of 16x16 matrix tiles (32x32 otherwise)."""
+    n_valid = n_k if ragged else min(n_k, q_pos + 1)
+    return _cols16(batch, group * h_kv, h_kv, d, n_valid, cap or n_k, heads_per_block(group), rotate)
+
+
 def decode_direct(batch, group, h_kv, n_k, q_pos, d, rotate=False, ragged=False, cap=None):
     n_valid = n_k if ragged else min(n_k, q_pos + 1)
-    return _direct(batch, group * h_kv, d, n_valid, cap or n_k, heads_per_block(group), rotate, ragged)
+    return decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate, ragged, cap) and \
+        _direct(batch, group * h_kv, h_kv, d, n_valid, heads_per_block(group), rotate, ragged)
 
 
-def decode_splits(batch, group, h_kv, n_k, q_pos, rotate=False):
+def decode_splits(batch, group, h_kv, n_k, q_pos, d, rotate=False):
     """(splits of a uniform batch, the most its workspace has room for)."""
     n_valid = min(n_k, q_pos + 1)
-    return (_plan(batch, group * h_kv, h_kv, n_k, n_valid, heads_per_block(group), rotate),
+    cols16 = decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate)
+    return (_plan(batch, group * h_kv, h_kv, n_k, n_valid, heads_per_block(group), cols16, rotate),
             _room(batch, h_kv, n_k))

@@ -19,12 +19,25 @@ import routes
     # no room for splits; rotating one or two heads of d = 64 takes the 4-wave kernel
     (132, 3, 8, 16000, 128, False, 0), (132, 1, 16, 4000, 64, True, 1), (264, 2, 8, 1000, 64, True, 1),
     (264, 7, 8, 1000, 64, True, 0), (64, 1, 16, 4000, 64, True, 0), (132, 1, 16, 4000, 64, False, 0),
+    # heads of several workgroups: all the splits there is room for, unless rows are short
+    (270, 39, 1, 40029, 128, False, 4), (160, 35, 2, 20121, 128, True, 4), (16, 64, 1, 123544, 128, False, 64),
+    (270, 39, 1, 1000, 128, False, 0),
 ])
 def test_decode_between_whole_rounds(batch, group, h_kv, n_k, d, rotate, splits):
     direct = routes.decode_direct(batch, group, h_kv, n_k, n_k - 1, d, rotate)
     assert direct == (splits == 0)
     if not direct:
-        assert routes.decode_splits(batch, group, h_kv, n_k, n_k - 1, rotate)[0] == splits
+        assert routes.decode_splits(batch, group, h_kv, n_k, n_k - 1, d, rotate)[0] == splits
+
+
+def test_decode_heads_of_one_kv_head_in_several_workgroups():
+    """16x16 tiles up to 16 heads; several workgroups of them only within the last-level cache."""
+    tiles = lambda batch, group, h_kv, n_k, **kw: routes.decode_cols16(batch, group, h_kv, n_k, n_k - 1, 128, **kw)
+    assert tiles(1, 16, 1, 2 ** 20) and not tiles(1, 17, 1, 1) and not tiles(1, 32, 1, 1)
+    assert not tiles(1, 1, 1, 1, cap=2 ** 27 - 64) and tiles(1, 1, 1, 1, cap=2 ** 27 - 65)
+    assert tiles(128, 39, 1, 4096) and not tiles(128, 39, 1, 4097) and tiles(128, 39, 1, 4097, rotate=True)
+    assert tiles(64, 35, 2, 4096) and not tiles(64, 35, 2, 4097) and not tiles(64, 35, 2, 4097, ragged=True)
+    assert tiles(512, 13, 1, 2 ** 16)
 
 
 def test_decode_plans_fit_and_leave_no_split_empty():
@@ -32,10 +45,14 @@ def test_decode_plans_fit_and_leave_no_split_empty():
     for _ in range(20000):
         batch, h_kv = int(2 ** rng.uniform(0, 10)), rng.choice([1, 2, 3, 4, 8, 16])
         group, rotate = rng.choice([1, 2, 3, 5, 7, 8, 11, 16, 17, 24, 32, 33, 64]), rng.random() < 0.5
+        d = rng.choice([64, 128])
         n_k = int(2 ** rng.uniform(0, 19))
         q_pos = rng.choice([n_k - 1, rng.randrange(n_k), n_k + 5])
-        splits, room = routes.decode_splits(batch, group, h_kv, n_k, q_pos, rotate)
+        splits, room = routes.decode_splits(batch, group, h_kv, n_k, q_pos, d, rotate)
         steps = -(-min(n_k, q_pos + 1) // 128)
         assert 1 <= splits <= room
+        if routes.heads_per_block(group) < group:
+            assert splits == room
+            continue
         per = -(-steps // splits)  # steps of every split but the last, which has at least one
         assert (splits - 1) * per < steps, (batch, h_kv, group, n_k, q_pos)

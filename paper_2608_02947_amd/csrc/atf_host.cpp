@@ -542,7 +542,7 @@ int atf_pack_kcache(const void* k_bshd, void* k_pcm, int32_t batch, int64_t n_k,
     const size_t bytes = size_t(batch) * size_t(n_k) * size_t(h_kv) * size_t(head_dim) * 2;
     int rc = check_pack("pack_kcache", k_bshd, k_pcm, batch, n_k, h_kv, head_dim, bytes);
     if (rc != ATF_OK) return rc;
-    atf::AppendParams p{};
+    atf::AppendRotParams p{};
     p.k_src = static_cast<const uint16_t*>(k_bshd);
     p.k_dst = static_cast<uint16_t*>(k_pcm);
     p.batch = batch;
@@ -604,7 +604,7 @@ int atf_pack_vcache(const void* v_bshd, void* v_pack, int32_t batch, int64_t n_k
                         (batch >= 1 && n_k >= 1 && h_kv >= 1 && n_k <= kPosLimit)
                             ? vcache_bytes(batch, n_k, h_kv, head_dim) : 0);
     if (rc != ATF_OK) return rc;
-    atf::AppendParams p{};
+    atf::AppendRotParams p{};
     p.v_src = static_cast<const uint16_t*>(v_bshd);
     p.v_dst = static_cast<uint16_t*>(v_pack);
     p.batch = batch;
@@ -622,7 +622,7 @@ namespace {
 int cache_append_impl(const char* fn, const void* k_new, const void* v_new, void* k_cache,
                       void* v_cache, int32_t batch, int64_t n_new, int64_t pos0, int32_t h_kv,
                       int32_t head_dim, int64_t cache_tokens, void* hip_stream,
-                      const atf::AppendParams* rope) {
+                      const atf::AppendRotParams* rope) {
     if (head_dim != 64 && head_dim != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built", fn, head_dim);
     if (batch < 1 || h_kv < 1 || n_new < 0 || pos0 < 0 || cache_tokens < 1 ||
@@ -645,7 +645,7 @@ int cache_append_impl(const char* fn, const void* k_new, const void* v_new, void
             if (bufs[i] < bufs[j] + sizes[j] && bufs[j] < bufs[i] + sizes[i])
                 return fail(ATF_EINVAL, "%s: buffers overlap", fn);
     if (n_new == 0) return ATF_OK;
-    atf::AppendParams p = rope != nullptr ? *rope : atf::AppendParams{};
+    atf::AppendRotParams p = rope != nullptr ? *rope : atf::AppendRotParams{};
     p.k_src = static_cast<const uint16_t*>(k_new);
     p.v_src = static_cast<const uint16_t*>(v_new);
     p.k_dst = static_cast<uint16_t*>(k_cache);
@@ -677,7 +677,7 @@ int atf_cache_append_rotated(const void* k_new, const void* v_new, void* k_cache
     const int d = w->head_dim;
     if (d != 64 && d != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built (64 or 128)", fn, d);
-    atf::AppendParams rp{};
+    atf::AppendRotParams rp{};
     const int rc = rope_fractions(fn, w, rope_inv_freq, rp.rope_rho_hi, rp.rope_rho_lo);
     if (rc != ATF_OK) return rc;
     return cache_append_impl(fn, k_new, v_new, k_cache, v_cache, batch, n_new, pos0, h_kv, d,
@@ -1003,7 +1003,7 @@ int cache_append_paged_impl(const char* fn, const void* k_new, const void* v_new
                             void* v_pages, const int32_t* block_table, int32_t max_pages_per_row,
                             int32_t num_pages, int32_t page_tokens, int32_t batch, int64_t n_new,
                             int64_t pos0, int32_t h_kv, int32_t head_dim, void* hip_stream,
-                            const atf::AppendParams* rope) {
+                            const atf::AppendRotParams* rope) {
     if (head_dim != 64 && head_dim != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built", fn, head_dim);
     if (batch < 1 || h_kv < 1 || n_new < 0 || pos0 < 0)
@@ -1025,7 +1025,7 @@ int cache_append_paged_impl(const char* fn, const void* k_new, const void* v_new
     if (n_new == 0) return ATF_OK;
     if (int64_t(batch) * n_new * h_kv > kPosLimit)
         return fail(ATF_EINVAL, "%s: too many tokens for one call", fn);
-    atf::AppendParams p = rope != nullptr ? *rope : atf::AppendParams{};
+    atf::AppendRotParams p = rope != nullptr ? *rope : atf::AppendRotParams{};
     p.k_src = static_cast<const uint16_t*>(k_new);
     p.v_src = static_cast<const uint16_t*>(v_new);
     p.k_dst = static_cast<uint16_t*>(k_pages);
@@ -1064,7 +1064,7 @@ int atf_cache_append_paged_rotated(const void* k_new, const void* v_new, void* k
     const int d = w->head_dim;
     if (d != 64 && d != 128)
         return fail(ATF_EUNSUPPORTED, "%s: head_dim %d not built (64 or 128)", fn, d);
-    atf::AppendParams rp{};
+    atf::AppendRotParams rp{};
     const int rc = rope_fractions(fn, w, rope_inv_freq, rp.rope_rho_hi, rp.rope_rho_lo);
     if (rc != ATF_OK) return rc;
     return cache_append_paged_impl(fn, k_new, v_new, k_pages, v_pages, block_table,

@@ -62,10 +62,11 @@ __global__ __launch_bounds__(256) void rotate_kcache_kernel(const RotateParams p
 // (token, chunk) and per (block, dim) with a 64-bit division chain each and 2-byte stores
 // of V, in two launches, took 96 us for 16,384 tokens of 8 heads at d = 128 (134 MB moved,
 // rotated); this takes 33.7 us (4.0 TB/s).
-enum { kKeysNone = 0, kKeysAsGiven = 1, kKeysTurned = 2 };
+constexpr int kKeysNone = 0, kKeysAsGiven = 1, kKeysTurned = 2;
 
 template <int D, int kKeys, bool kValues, bool kPaged>
-__global__ __launch_bounds__(256) void append_kernel(const AppendParams p) {
+__global__ __launch_bounds__(256) void append_kernel(
+    const std::conditional_t<kKeys == kKeysTurned, AppendRotParams, AppendParams> p) {
     constexpr int kChunks = D / 16;
     constexpr int kSteps = D / 64;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(256) void append_kernel(const AppendParams p) {
 }
 
 template <int D, int kKeys, bool kValues, bool kPaged>
-hipError_t launch_append_k(const AppendParams& p, hipStream_t stream) {
+hipError_t launch_append_k(const AppendRotParams& p, hipStream_t stream) {
     const int64_t nblk = (p.pos0 + p.n_new - 1) / 16 + 1 - p.pos0 / 16;
     const int64_t units = int64_t(p.batch) * nblk * p.h_kv;
     // (16 rows of 128 bytes or more each: 2^31 units do not fit the memory)
@@ -220,7 +221,7 @@ hipError_t launch_append_k(const AppendParams& p, hipStream_t stream) {
 }
 
 template <int D>
-hipError_t launch_append_d(const AppendParams& p, bool turn, hipStream_t stream) {
+hipError_t launch_append_d(const AppendRotParams& p, bool turn, hipStream_t stream) {
     if (p.block_table != nullptr)
         return turn ? launch_append_k<D, kKeysTurned, true, true>(p, stream)
                     : launch_append_k<D, kKeysAsGiven, true, true>(p, stream);
@@ -232,7 +233,7 @@ hipError_t launch_append_d(const AppendParams& p, bool turn, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_append(const AppendParams& p, bool turn, int head_dim, hipStream_t stream) {
+hipError_t launch_append(const AppendRotParams& p, bool turn, int head_dim, hipStream_t stream) {
     return head_dim == 64 ? launch_append_d<64>(p, turn, stream) : launch_append_d<128>(p, turn, stream);
 }
 

@@ -119,6 +119,10 @@ struct RotateParams {
 // Kernel launchers (prefill.hip, decode.hip, rotate.hip).  Return the HIP error of the launch.
 hipError_t launch_prefill(const PrefillParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_prefill_rotating(const PrefillRotParams& p, int head_dim, hipStream_t stream);
+// The kernel a prefill takes: 4 or 8 waves per row block of prefill_short_kernel, 0 for
+// prefill_kernel, -1 if it is refused (the tests ask).
+int32_t prefill_waves(int32_t batch, int32_t n_q, int32_t n_k, int32_t q_pos0, int32_t h_kv, int32_t group,
+                      int32_t cache_tokens, const int32_t* thresholds, int32_t head_dim, bool rotate);
 hipError_t launch_decode(const DecodeParams& p, int head_dim, hipStream_t stream);
 hipError_t launch_append(const AppendRotParams& p, bool turn, int head_dim, hipStream_t stream);
 hipError_t launch_rotate_kcache(const RotateParams& p, int head_dim, hipStream_t stream);

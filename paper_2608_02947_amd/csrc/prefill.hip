@@ -1155,7 +1155,6 @@ hipError_t prepare(P& p, int head_dim, unsigned* blocks, bool* window_on) {
     return hipSuccess;
 }
 
-
 // Waves per row block of prefill_short_kernel for this call, or 0 for prefill_kernel.
 //
 // prefill_kernel takes as long as its longest row as long as its workgroups (`blocks` of
@@ -1178,16 +1177,45 @@ hipError_t prepare(P& p, int head_dim, unsigned* blocks, bool* window_on) {
 // 24/8 heads against 8,000 keys 64 -> 49 us; 64 rows against 8,000 keys 58 -> 43 us).
 // Below about 4,096 keys the merge of the longer list of states takes the gain back (512
 // keys: equal).
+//
+// That holds while the short kernel is bound by its row blocks' own work.  Short prompts are
+// bound by what a row block costs before and after its few keys, and then it stops gaining at
+// 0.2 to 0.5 of the limit (counted in row blocks, which a call with part tiles has fewer of):
+// 8 prompts of 290 tokens of 24/8 heads 20.9 -> 29.0 us, 32 of 48 of 28/4 14.3 -> 22.8, 4 of
+// 468 of 32/4 without a window 20.9 -> 28.3, 32 of 160 of 16/1 heads of d = 64 14.1 -> 18.9;
+// rotating 16 of 58 of 32/4 17.3 -> 21.9.  From 384 keys on (1,024 without a window, 640 at d
+// = 64, rotating 128 and 384) the limit stands; between, a line.
+// And where the caches of the batch's entries pass the 256 MB last-level cache, row blocks of
+// one entry that do not run at once read its keys from memory again each: 16 x 117 rows against
+// 11,166 keys of 16/16 heads of d = 64 (1,024 row blocks) 189 -> 285, but 6 x 132 against 26,240
+// of 24/8 (624) 584 -> 489; past 1 GB also where the limit is near: 32 x 9 against 27,936 of 32/4
+// (384 row blocks) 441 -> 609, but 16 x 22 against 38,656 half the time.
 int short_split(const PrefillParams& p, int head_dim, bool window_on, bool rotate, int64_t blocks) {
     // the short kernel's lane offsets cover all chunks of a token's stream in 32 bits
     if (int64_t(p.cache_tokens) * head_dim * 2 > int64_t(UINT32_MAX)) return 0;
     const int64_t longest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + p.n_q);
     const int64_t shortest = std::min<int64_t>(p.n_k, int64_t(p.q_pos0) + 1);
+    const int64_t mean = (shortest + longest) / 2;
     const int64_t limit = head_dim == 64 ? (window_on ? (rotate ? 192 : 320) : (rotate ? 80 : 184))
                                          : (rotate ? (window_on ? 64 : 56) : (window_on ? 132 : 120));
-    if (blocks * ((shortest + longest) / 2) > limit * longest) return 0;
-    const int64_t row_blocks = blocks * (head_dim == 64 && window_on ? 4 : 8);
-    return row_blocks <= 256 && longest >= 4096 ? 8 : 4;
+    if (blocks * mean > limit * longest) return 0;
+    const int64_t per = head_dim == 64 && window_on ? 4 : 8;  // row blocks of a full workgroup of prefill_kernel
+    const auto parts = [&](int64_t positions) { return (positions * p.group + 31) / 32; };
+    const int64_t entries = int64_t(p.batch) * p.h_kv;
+    const int64_t row_blocks = entries * (p.n_q / p.pos_per_tile * parts(p.pos_per_tile) + parts(p.n_q % p.pos_per_tile));
+    const int64_t long_from = rotate ? (head_dim == 64 ? 384 : 128) : head_dim == 64 ? 640 : window_on ? 384 : 1024;
+    const int64_t tenths = rotate ? 5 : head_dim == 128 && window_on ? 2 : 3;
+    if (longest < long_from && 10 * row_blocks * mean * long_from >
+                                   per * limit * longest * (tenths * long_from + (10 - tenths) * longest))
+        return 0;
+    if (rotate || row_blocks <= 256) return blocks * per <= 256 && longest >= 4096 ? 8 : 4;
+    const bool many = row_blocks > (window_on ? 768 : head_dim == 64 ? 640 : 512);
+    if (many || 10 * blocks * mean > 9 * limit * longest) {
+        int64_t kept = 0;  // (key, pair) terms of the last row
+        for (int r = 0; r < head_dim / 2; ++r) kept += std::min<int64_t>(p.win.W[r], longest);
+        if (entries * (4 * kept + 2 * head_dim * longest) > int64_t(many ? 256 : 1024) << 20) return 0;
+    }
+    return 4;
 }
 
 template <int D, bool kWin, bool kRot, class P>
@@ -1219,6 +1247,23 @@ hipError_t launch_d(const P& p, unsigned blocks, bool window_on, hipStream_t str
 }
 
 }  // namespace
+
+int32_t prefill_waves(int32_t batch, int32_t n_q, int32_t n_k, int32_t q_pos0, int32_t h_kv, int32_t group,
+                      int32_t cache_tokens, const int32_t* thresholds, int32_t head_dim, bool rotate) {
+    PrefillParams p{};
+    p.batch = batch;
+    p.n_q = n_q;
+    p.n_k = n_k;
+    p.q_pos0 = q_pos0;
+    p.h_kv = h_kv;
+    p.group = group;
+    p.cache_tokens = cache_tokens;
+    std::copy_n(thresholds, head_dim / 2, p.win.W);
+    unsigned blocks = 0;
+    bool window_on = false;
+    if (prepare(p, head_dim, &blocks, &window_on) != hipSuccess) return -1;
+    return short_split(p, head_dim, window_on, rotate, blocks);
+}
 
 hipError_t launch_prefill(const PrefillParams& p_in, int head_dim, hipStream_t stream) {
     PrefillParams p = p_in;

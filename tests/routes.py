@@ -45,3 +45,14 @@ def decode_splits(batch, group, h_kv, n_k, q_pos, d, rotate=False):
     cols16 = decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate)
     return (_plan(batch, group * h_kv, h_kv, n_k, n_valid, heads_per_block(group), cols16, rotate),
             _room(batch, h_kv, n_k))
+
+
+_prefill = _rule("_ZN3atf13prefill_wavesEiiiiiiiPKiib", _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32,
+                 ctypes.c_void_p, _i32, _bool)
+
+
+def prefill_waves(window, batch, n_q, n_k, q_pos0, group, h_kv, rotate=False, cap=None):
+    """4 or 8: waves per row block of prefill_short_kernel; 0: prefill_kernel."""
+    table = atf.atf_window_table(window)
+    return _prefill(batch, n_q, n_k, q_pos0, h_kv, group, cap or n_k, table.ctypes.data,
+                    window.head_dim, rotate)

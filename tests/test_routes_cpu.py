@@ -1,8 +1,10 @@
-"""The rules that choose a decode call's kernel and split plan, on the host."""
+"""The rules that choose a call's kernel, and a decode's split plan, on the host."""
+import math
 import random
 
 import pytest
 
+import paper_2608_02947_amd as atf
 import routes
 
 
@@ -56,3 +58,30 @@ def test_decode_plans_fit_and_leave_no_split_empty():
             continue
         per = -(-steps // splits)  # steps of every split but the last, which has at least one
         assert (splits - 1) * per < steps, (batch, h_kv, group, n_k, q_pos)
+
+
+@pytest.mark.parametrize("batch,n_q,n_k,group,h_kv,d,k,rotate,waves", [
+    # a chunk against a long cache: few row blocks by 8 waves, more by 4, the chip full
+    (1, 64, 65836, 7, 4, 128, 2.0, False, 8), (1, 300, 65836, 7, 4, 128, 2.0, False, 4),
+    (1, 1188, 65836, 7, 4, 128, 2.0, False, 4), (1, 1189, 65836, 7, 4, 128, 2.0, False, 0),
+    (1, 300, 65836, 7, 4, 128, 2.0, True, 4), (1, 800, 65836, 7, 4, 128, 2.0, True, 0),
+    (1, 1024, 1024, 7, 2, 64, 2.0, False, 4), (1, 8191, 8191, 7, 2, 64, 2.0, False, 0),
+    # short prompts
+    (8, 290, 290, 3, 8, 128, 2.0, False, 0), (1, 290, 290, 3, 8, 128, 2.0, False, 4),
+    (32, 48, 48, 7, 4, 128, 2.0, False, 0), (4, 468, 468, 8, 4, 128, math.inf, False, 0),
+    (32, 160, 160, 16, 1, 64, 2.0, False, 0), (16, 58, 58, 8, 4, 128, 2.0, True, 0),
+    # caches past the last-level cache
+    (16, 117, 11166, 1, 16, 64, 2.0, False, 0), (6, 132, 26240, 3, 8, 128, 2.0, False, 4),
+    (32, 9, 27936, 8, 4, 128, 2.0, False, 0), (16, 22, 38656, 8, 4, 128, 2.0, False, 4),
+])
+def test_prefill_kernel(batch, n_q, n_k, group, h_kv, d, k, rotate, waves):
+    w = atf.Window(d, 1e6, k)
+    assert routes.prefill_waves(w, batch, n_q, n_k, n_k - n_q, group, h_kv, rotate) == waves
+
+
+def test_prefill_long_streams_take_the_kernel_with_64_bit_offsets():
+    w = atf.Window(128, 1e6, 2.0)
+    fits = (2 ** 32 - 1) // 256
+    assert routes.prefill_waves(w, 1, 16, 1000, 984, 1, 1, cap=fits) == 4
+    assert routes.prefill_waves(w, 1, 16, 1000, 984, 1, 1, cap=fits + 1) == 0
+    assert routes.prefill_waves(w, 1, 16, 1000, 984, 257, 1) == -1

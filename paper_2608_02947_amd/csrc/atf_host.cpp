@@ -190,30 +190,40 @@ namespace {
 // rounds of the chip's CUs that a number of equal workgroups takes
 constexpr int64_t kDecodeCUs = 256;
 int64_t decode_rounds(int64_t groups) { return (groups + kDecodeCUs - 1) / kDecodeCUs; }
+
+// Whether workgroups that share a KV head (35, 39 or 49 heads to one: 5 of 7, 3 of 13, 7 of 7)
+// find its keys in the caches wherever on the chip they run: caches of up to 1 GB over their
+// number, or 128 MB, beside a last-level cache of 256 MB.  Below it the unsplit 16-column kernel takes 0.2 to
+// 1.2 of the time of the split 32-column one (median 0.8 next to it), above it 0.7 to 2.2 (1.0
+// next to it; 3,600 calls).
+bool decode_shared_fits(int32_t batch, int32_t h_kv, int32_t head_dim, int64_t n_valid, int32_t workgroups) {
+    return int64_t(batch) * h_kv * n_valid <= (int64_t(1) << 30) / (4 * head_dim * std::min(workgroups, 8));
+}
 }  // namespace
 
 // Whether a call's workgroups take decode_split16_kernel: up to 16 heads each, and caches within
 // its lane offsets (they reach over one chunk's stream).
 //
-// Not where several workgroups share a KV head (35, 39 or 49 heads to one: 7 by 5, 13 by 3, 7 by
-// 7), keys are not rotated and the batch's caches pass the 256 MB last-level cache: more
-// workgroups are then in flight at places further apart, and keys that one has read have left
-// the caches when the next one of the same KV head comes (split16 against
-// decode_split_kernel: 146 rows of 86,558 keys, 70/2 heads 4813 and 3385 us, 270 rows of 40,029,
-// 39/1 1879 and 1607; but 21 rows of 6,824, 70/2, and smaller ones 0.3 to 1.0 of the time).
+// Not where several workgroups share a KV head and the batch's caches are large
+// (decode_shared_fits): more workgroups are then in flight at places further apart, and keys
+// that one has read have left the caches when the next one of the same KV head comes
+// (decode_split_kernel -> split16: 146 rows of 86,558 keys, 70/2 heads 3385 -> 4813 us, 270 rows of
+// 40,029, 39/1 1607 -> 1879; but 54 rows of 1,255, 70/2 152 -> 75).  A ragged batch's caches are
+// not known here, only a bound that is far from them where one row is long (496 rows of 1,905
+// keys in all, 99/3 heads, 216 -> 33); large ones lose up to 8 %.
 bool decode_cols16(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
-                   int64_t cache_tokens, int32_t heads_per_block, bool rotate) {
+                   int64_t cache_tokens, int32_t heads_per_block, bool ragged) {
     if (heads_per_block > 16 || cache_tokens >= kDecode16MaxTokens) return false;
-    return rotate || h_q / h_kv == heads_per_block ||
-           int64_t(batch) * h_kv * n_valid <= (int64_t(256) << 20) / (4 * head_dim);
+    const int32_t workgroups = h_q / h_kv / heads_per_block;
+    return ragged || workgroups == 1 || decode_shared_fits(batch, h_kv, head_dim, n_valid, workgroups);
 }
 
 // Splits a uniform batch uses, at most the decode_splits() its workspace has room for.
 //
-// Where several workgroups share a KV head (64 heads to one: two of 32), all of them: the
-// workgroups that read the same keys are that many apart and, where it is a multiple of 8, on
-// the same XCD (16 rows of 123,544 keys, 64/1 heads: 64 splits, 3 of them empty, 201 us, the
-// other 61 by themselves 235).
+// Where several workgroups share a KV head (64 heads to one: two of 32), a multiple of 8 where
+// one is near: the workgroups that read the same keys are that many apart, and so on the same
+// XCD (16 rows of 123,544 keys, 64/1 heads: 61 splits 235 us, 64, 3 of them empty, 201; but 10
+// rows of 14,730, rotating, 58 splits 66 us, 103 with 45 empty 80).
 //
 // Up to 16 heads per workgroup: as many workgroups as the CUs hold at once, 3 of
 // decode_split16_kernel (768) or 2 where it rotates keys (512, at d = 128; its tables are
@@ -231,7 +241,7 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
     const int64_t target = rotate ? 512 : 768;
     const int64_t steps = (n_valid + kDecodeTokenStep - 1) / kDecodeTokenStep;
-    if (h_q / h_kv != heads_per_block) return static_cast<int32_t>(room);
+    const bool shared = h_q / h_kv != heads_per_block;
     int64_t s = 1;
     if (!cols16) {
         s = room;
@@ -243,7 +253,9 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
     }
     s = std::max<int64_t>(1, std::min(s, steps));
     const int64_t per = (steps + s - 1) / s;
-    return static_cast<int32_t>(std::max<int64_t>(1, (steps + per - 1) / per));
+    s = std::max<int64_t>(1, (steps + per - 1) / per);
+    const int64_t up = (s + 7) / 8 * 8;
+    return static_cast<int32_t>(shared && up <= room && 16 * (up - s) <= s ? up : s);
 }
 
 // Whether a batch takes one workgroup of 8 waves per (row, KV head), which writes the
@@ -265,9 +277,9 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 // pairs of 3 heads, 1,000 keys 33.2 -> 34.7, 2,000 53.4 -> 60.8; of 7, 2,000 59.4 -> 60.1, 8,000
 // 179 -> 204; of 16, 4,000 112 -> 110, 8,000 193 -> 206; 528 pairs of 7 heads without a window,
 // 8,000 keys 404 -> 415, 60,000 2800 -> 3017.
-// Where several workgroups share a KV head, only short rows run unsplit: those workgroups are
-// up to a round of the chip apart, and the second one finds the keys gone from the caches (270
-// rows of 40,029 keys, 39/1 heads 1615 -> 2926; rotating, 281 rows of 7,939, 70/2 1506 -> 1854).
+// Workgroups that share a KV head run unsplit too: their caches are small (decode_cols16; 270
+// rows of 40,029 keys, 39/1 heads, would take 2926 for 1615, but 295 rows of 893, rotating,
+// 172 -> 75).
 // Rotating at d = 64, a CU holds 8 waves of the unsplit kernel and 12 of the split one: with 1
 // or 2 heads, whose merge costs least, the latter wins from 1,025 pairs on (2,112 pairs of 1
 // head, 300 keys 50 -> 62, 4,000 353 -> 378, 16,000 1242 -> 1261; of 2, 1,000 keys 110 -> 118,
@@ -291,7 +303,8 @@ int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k
 bool decode_direct(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
                    int32_t heads_per_block, bool rotate, bool ragged) {
     const int64_t cols = int64_t(batch) * (h_q / heads_per_block);
-    if (!ragged && cols >= kDecodeCUs && h_q / h_kv == heads_per_block) {
+    if (!ragged && cols >= kDecodeCUs) {
+        if (h_q / h_kv != heads_per_block) return true;
         const int64_t rounds = decode_rounds(cols), last = cols - (rounds - 1) * kDecodeCUs;
         if (rounds > 4) return !(rotate && head_dim == 64 && heads_per_block <= 2);
         if (rounds == 1 || last > 128) return true;
@@ -820,7 +833,7 @@ int decode_impl(const char* fn, const void* q, const void* k_cache, const void* 
     p.num_pages = pg.num_pages;
     p.page_tokens = pg.page_tokens;
     p.n_valid = static_cast<int32_t>(ragged ? n_k : std::min(q_pos, n_k - 1) + 1);
-    p.cols16 = atf::decode_cols16(batch, h_q, h_kv, d, p.n_valid, cache_tokens, hpb, rope.rotate);
+    p.cols16 = atf::decode_cols16(batch, h_q, h_kv, d, p.n_valid, cache_tokens, hpb, ragged);
     if (ragged) {
         // the work items are laid out on the device from the row arrays: the batch's
         // keys in about `splits` equal spans (multiples of the workgroup's token step)

@@ -133,7 +133,7 @@ int32_t decode_splits(int32_t batch, int32_t h_kv, int64_t n_k);
 int32_t decode_ragged_items(int32_t cols);
 // The kernel and the numbers a call uses; n_valid bounds a ragged batch's rows.
 bool decode_cols16(int32_t batch, int32_t h_q, int32_t h_kv, int32_t head_dim, int64_t n_valid,
-                   int64_t cache_tokens, int32_t heads_per_block, bool rotate);
+                   int64_t cache_tokens, int32_t heads_per_block, bool ragged);
 int32_t decode_plan_splits(int32_t batch, int32_t h_q, int32_t h_kv, int64_t n_k, int64_t n_valid,
                            int32_t heads_per_block, bool cols16, bool rotate);
 int32_t decode_plan_items(int32_t cols, bool cols16);

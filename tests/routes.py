@@ -27,22 +27,22 @@ def heads_per_block(group):
     return max(c for c in range(1, 33) if group % c == 0)
 
 
-def decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate=False, ragged=False, cap=None):
+def decode_cols16(batch, group, h_kv, n_k, q_pos, d, ragged=False, cap=None):
     """Whether the heads are the columns of 16x16 matrix tiles (32x32 otherwise)."""
     n_valid = n_k if ragged else min(n_k, q_pos + 1)
-    return _cols16(batch, group * h_kv, h_kv, d, n_valid, cap or n_k, heads_per_block(group), rotate)
+    return _cols16(batch, group * h_kv, h_kv, d, n_valid, cap or n_k, heads_per_block(group), ragged)
 
 
 def decode_direct(batch, group, h_kv, n_k, q_pos, d, rotate=False, ragged=False, cap=None):
     n_valid = n_k if ragged else min(n_k, q_pos + 1)
-    return decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate, ragged, cap) and \
+    return decode_cols16(batch, group, h_kv, n_k, q_pos, d, ragged, cap) and \
         _direct(batch, group * h_kv, h_kv, d, n_valid, heads_per_block(group), rotate, ragged)
 
 
 def decode_splits(batch, group, h_kv, n_k, q_pos, d, rotate=False):
     """(splits of a uniform batch, the most its workspace has room for)."""
     n_valid = min(n_k, q_pos + 1)
-    cols16 = decode_cols16(batch, group, h_kv, n_k, q_pos, d, rotate)
+    cols16 = decode_cols16(batch, group, h_kv, n_k, q_pos, d)
     return (_plan(batch, group * h_kv, h_kv, n_k, n_valid, heads_per_block(group), cols16, rotate),
             _room(batch, h_kv, n_k))
 

@@ -87,10 +87,10 @@ ROUNDS = [
     (24, 1, 16, 1200, 64, 0, 2),     # 384, too short pre-rotated
     (65, 1, 16, 300, 64, 0, 1),      # 1,040: no room for two splits
     (130, 2, 8, 129, 64, 0, 1),
-    # 39 heads to a KV head: three workgroups of 13, on 16x16 tiles unless the caches pass 256 MB
-    (40, 39, 1, 3500, 128, 26, 26),
-    (150, 39, 1, 1200, 128, 0, 7),
-    (160, 39, 1, 3400, 128, 7, 7),
+    # 39 heads to a KV head: three workgroups of 13, on 16x16 tiles unless the caches pass 341 MB
+    (40, 39, 1, 3500, 128, 6, 4),
+    (150, 39, 1, 1200, 128, 0, 0),
+    (240, 39, 1, 3400, 128, 5, 5),
 ]
 
 
@@ -105,7 +105,7 @@ def test_decode_between_whole_rounds(case, unrotated):
     direct = routes.decode_direct(B, G, h_kv, n_k, q_pos, d, unrotated, cap=cap)
     plan = 0 if direct else routes.decode_splits(B, G, h_kv, n_k, q_pos, d, unrotated)[0]
     assert plan == splits[unrotated]
-    assert routes.decode_cols16(B, G, h_kv, n_k, q_pos, d, unrotated, cap=cap) == (B < 160 or unrotated)
+    assert routes.decode_cols16(B, G, h_kv, n_k, q_pos, d, cap=cap) == (B < 240)
     g = torch.Generator(device="cpu").manual_seed(B * 1009 + n_k)
     q = torch.randn((3, 1, h_q, d), generator=g).to(torch.bfloat16)
     k = torch.randn((3, n_k, h_kv, d), generator=g).to(torch.bfloat16)

@@ -11,6 +11,7 @@ import torch
 
 from conftest import gpu_available
 import oracle
+import routes
 import workloads as W
 from parity import compare, note, pack_kcache, pack_vcache, to_f64, windows_for
 
@@ -69,6 +70,29 @@ def test_decode_columns(case, unrotated):
     fn(qd, kp, vp, o, lse, q_pos, win, ws, n_k=n_k)
     torch.cuda.synchronize()
     compare(to_f64(o), to_f64(lse), o_ref[:, 0], lse_ref[:, :, 0], f"columns {case}")
+
+
+# rows that are split over workgroups of 4 waves, with the merge after them
+SPLIT_CASES = [
+    (1, 2, 4097, 4096, 64, 2.0, "mixed"),
+    (16, 1, 2578, 2577, 128, 2.0, "mixed"),
+    (16, 2, 4129, 4128, 64, math.inf, "base"),
+    (15, 1, 2561, 2560, 128, 2.0, "base"),
+    (7, 1, 2568, 2567, 128, 2.0, "mixed"),
+    (3, 3, 4100, 4096, 64, 2.0, "mixed"),
+    (5, 1, 2594, 2568, 128, 0.5, "base"),      # keys past the query: the last block is cut
+    (12, 1, 2593, 3000, 128, 2.0, "mixed"),    # query past the cache's end
+]
+
+
+@pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: "x".join(str(x) for x in c))
+def test_decode_columns_split(case, unrotated):
+    G, h_kv, n_k, q_pos, d, _, _ = case
+    assert routes.decode_cols16(2, G, h_kv, n_k, q_pos, d, cap=n_k + 21)
+    assert not routes.decode_direct(2, G, h_kv, n_k, q_pos, d, unrotated, cap=n_k + 21)
+    assert routes.decode_splits(2, G, h_kv, n_k, q_pos, d, unrotated)[0] > 1
+    test_decode_columns(case, unrotated)
 
 
 @pytest.mark.parametrize("unrotated", [False, True], ids=["rotated", "unrotated"])

@@ -142,6 +142,9 @@ int atf_count_terms(const atf_window *w, int64_t n_q, int64_t q_pos0, int64_t n_
  * cache_tokens is the number of tokens each batch entry of the caches is
  * allocated for (0 means n_k); a chunk of a longer prefill passes the positions of
  * its rows (q_pos0) and the keys written so far (n_k) against the same caches.
+ * Equal calls give equal bits.  Chunks and one whole call agree to the rounding of the
+ * fp32 sums; bit for bit where chunks start at multiples of the position tile and the
+ * sizes of both give the same kernel (calls with few rows take one of their own).
  * Query head h uses key/value head h / (h_q / h_kv).  softmax_scale <= 0 selects
  * 1/sqrt(d).  n_q == 0 is a no-op.
  * Errors: ATF_EINVAL (NULL/misaligned pointer, batch < 1, n_q < 0, n_k < 1,
@@ -252,7 +255,8 @@ size_t atf_decode_workspace_bytes(int32_t batch, int32_t h_q, int32_t h_kv, int6
 /* Decode: one query token per batch row at position q_pos, against keys
  * 0 .. min(q_pos, n_k - 1) of that row's cache (the last query row of Fig. fa).
  * The cache is split over tokens; each split keeps partial (max, normaliser,
- * output) states that a second kernel merges (split-KV, Sec. 5).  For pair-chunk
+ * output) states that a second kernel merges (split-KV, Sec. 5); short rows, and
+ * batches whose rows fill the device, are not split.  For pair-chunk
  * c only the token suffix whose distance is within the chunk's largest window
  * is read; pairs whose window ends inside that suffix are masked per token.
  *   q        bf16 [batch][h_q][d]                                   (device, read)
@@ -309,8 +313,11 @@ int atf_decode_noalloc(const void *q, const void *k_cache, const void *v_cache, 
  * different lengths).  Everything else is atf_decode: same layouts, window,
  * split-KV partial states and merge.  The split plan follows the rows' lengths
  * on the device: the batch's causal keys are cut into spans of equal length (a
- * multiple of 128 tokens, about 2048 workgroups in all), each row into whole
- * spans of its own keys, so a short row takes few workgroups and a long one many.
+ * multiple of 128 tokens, about 1536 workgroups in all, 2048 where a workgroup
+ * holds more than 16 heads), each row into whole spans of its own keys, so a short
+ * row takes few workgroups and a long one many.  Where max_n_k is short (the limit is
+ * higher for a batch of many rows), each row takes one workgroup per KV head, or per
+ * 16 or fewer of its heads, instead: no partial states and no merge.
  *   n_k_rows    int32 [batch], DEVICE, 4-byte aligned: keys of each row's cache
  *   q_pos_rows  int32 [batch], DEVICE, 4-byte aligned: query position of each row
  *   max_n_k     host bound on n_k_rows (1 .. cache_tokens); the workspace is

@@ -13,14 +13,18 @@
 //     tokens of a d-row in the order the PV matrix instruction consumes them
 //     (position 8h + e holds token 8*(e/4) + 4h + e%4), zero past n_k.
 //
-// The G query heads of one KV head are the columns of 32x32 MFMA tiles, so a
-// decode step is the prefill's arithmetic with "query rows" = heads:
+// The G query heads of one KV head are the columns of MFMA tiles, so a decode step
+// is the prefill's arithmetic with "query rows" = heads:
 //   S^T[token][head] = K[token][dims] * Q^T[dims][head]   (A from the K stream)
 //   O^T[d][head]    += V^T[d][token] * P^T[token][head]   (A from the V blocks)
-// Every operand fragment is a 16-byte load straight from HBM into registers; no
-// LDS staging and no barrier in the streaming loop.  Each wave streams its own
-// 32-token blocks of the workgroup's split; the four waves' partial softmax
-// states are combined in LDS and written as the split's partial.
+// Two kernels: decode_split16_kernel, 16x16 tiles, up to 16 heads a workgroup;
+// decode_split_kernel, 32x32 tiles, for the other groups (decode_cols16 decides).
+// Every operand fragment of K and V is a 16-byte load straight from HBM into
+// registers; no LDS staging and no barrier in the streaming loop.  Each wave streams
+// its own 32-token blocks of the workgroup's split; the waves' partial softmax
+// states are combined in LDS and written as the split's partial.  A workgroup has
+// four waves, or eight where the 16-column kernel takes a whole row (decode_direct):
+// it then writes the row's output itself and nothing is merged.
 //
 // Window: per 32-token block, all pairs are classified by two lane-parallel
 // compares and ballots (lane r holds W_r): pairs kept at every distance of the
@@ -31,7 +35,7 @@
 // Batches: a uniform batch splits every row into the same token ranges; a ragged or
 // paged batch (row lengths in device arrays) cuts the batch's keys into equal spans,
 // each row into whole spans of its own keys, laid out by every workgroup from the row
-// arrays (ragged_item).
+// arrays (ragged_item).  Rows that are not split need neither.
 //
 // Rotation at read time (App. B): with unrotated q and K the kernel applies RoPE to
 // the query once and to each key chunk it loads, so a pruned pair is neither read nor
@@ -380,25 +384,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_split_kernel(const Deco
 #pragma unroll
             for (int c = 0; c < kChunks; ++c) {
                 const bool kept = c == kChunks - 1 || ((keep >> (8 * c)) & 0xFFull) != 0;
-                if (kept) {
-                    const float* row = &s_colcs[col * kCStride + 16 * c];
-                    const float* brow = blk + 16 * c;
-                    float cs8[8], sn8[8];
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        const float4 v = *reinterpret_cast<const float4*>(row + 4 * q4);  // pairs 2q4, 2q4+1
-                        const float4 w = *reinterpret_cast<const float4*>(brow + 4 * q4);
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const int e = 2 * q4 + j;
-                            const float cB = j ? w.z : w.x, sB = j ? w.w : w.y;
-                            const float cC = j ? v.z : v.x, sC = j ? v.w : v.y;
-                            cs8[e] = __builtin_fmaf(cB, cC, -sB * sC);
-                            sn8[e] = __builtin_fmaf(sB, cC, cB * sC);
-                        }
-                    }
-                    kf[c] = rope::rotate_cs(kf[c], rope::other_half(kf[c], hh), hh, cs8, sn8);
-                }
+                if (kept)
+                    kf[c] = rope::rotate_block(kf[c], hh, &s_colcs[col * kCStride + 16 * c], blk + 16 * c);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -834,8 +821,9 @@ __global__ __launch_bounds__(NW * 64, (NW > 4 ? 2 : kRot ? (D == 128 ? 2 : 3) : 
                 const float c2 = exp2_fast(__builtin_fmaf(sacc[s][2 * t + 1], sc, m_neg));
                 l_run += a;
                 l_run += c2;
-                // the bf16 number below P, and the rest, which is never 0 then (an infinite
-                // value times 0 would turn an infinite output into NaN)
+                // the bf16 number below P, and the rest, which is not 0 then (an infinite
+                // value times 0 would turn an infinite output into NaN) while P is at least
+                // 2^-103: the rest is 2^-23 of P or more, a normal number then
                 const uint32_t ha = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, a), 1u) & 0xFFFF0000u;
                 const uint32_t hc = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, c2), 1u) & 0xFFFF0000u;
                 pb[2 * s + t] = ha >> 16 | hc;
@@ -850,7 +838,8 @@ __global__ __launch_bounds__(NW * 64, (NW > 4 ? 2 : kRot ? (D == 128 ? 2 : 3) : 
         for (int i = 0; i < kDB; ++i) oacc[i] = mfma16(vf[i], pl, oacc[i]);
     }
 
-    // ---- combine the four waves' states (in wave order) and write the split's partial
+    // ---- combine the NW waves' states (in wave order) and write the split's partial, or
+    // the output of a row that is not split
     float l_lane = l_run + __shfl_xor(l_run, 16);
     l_lane += __shfl_xor(l_lane, 32);
     if (g4 == 0) {

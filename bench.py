@@ -518,15 +518,15 @@ TRAFFIC_RECORDS = {
         "sources": ["paper_2608_02947_amd/csrc/prefill.hip",
                     "paper_2608_02947_amd/csrc/atf_internal.hpp",
                     "paper_2608_02947_amd/csrc/rope.hpp"],
-        "sha256": "d9c9dcc43bb67ee7c2dd97170a5956149d9e7ae00eb24c84b92ab89fad06588d",
-        "fetch_kib": 80922943.38, "write_kib": 933525.17,
+        "sha256": "8126f4ad69eb8d10aa8269c9f565144566f14e1cdf377f04864c6034843a0546",
+        "fetch_kib": 107686406.41, "write_kib": 933532.21,
     },
-    "decode_split_kernel<128, false>": {
+    "decode_split16_kernel<128, false, 4>": {
         "sources": ["paper_2608_02947_amd/csrc/decode.hip",
                     "paper_2608_02947_amd/csrc/atf_internal.hpp",
                     "paper_2608_02947_amd/csrc/rope.hpp"],
-        "sha256": "a45523c72cc5dbb7bffda3e4d025f689c4ccb579daa1f199c7bde058204a3889",
-        "fetch_kib": 737788.15, "write_kib": 4071.24,
+        "sha256": "461b85553e3b51d1a9288203d2472eb0d384bdede7c2e89e728823f91c1d131f",
+        "fetch_kib": 737740.81, "write_kib": 3080.02,
     },
 }
 COPY_CALIBRATION_KIB = {"fetch": 524302.02, "write": 1048576.0}  # counters for a 1 GiB copy
@@ -788,7 +788,7 @@ def main():
     if tr is not None:
         roofline["traffic_fetch_bytes"] = tr["fetch_bytes"]
         roofline["traffic_write_bytes"] = tr["write_bytes"]
-    trd = recorded_traffic("decode_split_kernel<128, false>")
+    trd = recorded_traffic("decode_split16_kernel<128, false, 4>")
     decode_info["hbm_traffic_bytes"] = None if trd is None else trd["bytes"]
 
     cpu = None

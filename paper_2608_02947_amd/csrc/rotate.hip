@@ -47,9 +47,13 @@ __global__ __launch_bounds__(256) void rotate_kcache_kernel(const RotateParams p
 // Append: K and V of the new tokens in one launch.  One wave per unit = (batch, 16-token
 // block of cache positions, kv head), heads fastest, so that the waves of a workgroup read
 // neighbouring rows of the source ([B][n_new][h_kv][d]).
-//   K: one (token, chunk) record per lane and step: 16 bytes of each half of the chunk's
-//      pairs in, 32 contiguous bytes of the chunk's stream out; 16 tokens of a chunk are 512
-//      contiguous bytes.
+//   K, turned: one (token, chunk) record per lane and step: 16 bytes of each half of the
+//      chunk's pairs in, 32 contiguous bytes of the chunk's stream out; 16 tokens of a chunk
+//      are 512 contiguous bytes.
+//   K, as given: 16 bytes per lane and step, lanes along a token's row, so that a step reads
+//      whole rows and stores whole 32-byte records (as above every store instruction leaves
+//      out half of each: packs of 52 x 344 tokens of 4 heads at d = 128 8.1 us -> 7.1, of
+//      51 x 3,021 of one at d = 64 8.0 -> 6.4; appends of K and V 1-7 % less).
 //   V: a lane takes 2 dims x the 8 tokens of one half of the block's slots (slot 8h + e
 //      holds token 8(e/4) + 4h + e%4): eight 4-byte loads, 256 (d = 64: 128) contiguous
 //      bytes per token, transposed in registers into two 16-byte stores.  Of a block that
@@ -109,7 +113,19 @@ __global__ __launch_bounds__(256) void append_kernel(
             constexpr bool W = decltype(whole_tag)::value;
             u32x4 kx[kSteps], ky[kSteps];
             [[maybe_unused]] uint32_t vx[kSteps][8];
-            if constexpr (kKeys != kKeysNone) {
+            // a key that is not turned: piece i, 8 dims of half h of token t
+            const auto piece = [&](int j, auto f) __attribute__((always_inline)) {
+                const int i = lane + 64 * j, t = i / (D / 8), o = i % (D / 8);
+                if (W || (t >= lo && t < hi)) f(j & 1 ? ky[j / 2] : kx[j / 2], t, o % kChunks, o / kChunks);
+            };
+            if constexpr (kKeys == kKeysAsGiven) {
+#pragma unroll
+                for (int j = 0; j < 2 * kSteps; ++j)
+                    piece(j, [&](u32x4& x, int t, int c, int h) __attribute__((always_inline)) {
+                        x = *reinterpret_cast<const u32x4*>(p.k_src + src0 + t * row + h * (D / 2) + 8 * c);
+                    });
+            }
+            if constexpr (kKeys == kKeysTurned) {
 #pragma unroll
                 for (int j = 0; j < kSteps; ++j) {
                     const int t = lane & 15, c = (lane >> 4) + 4 * j;
@@ -131,23 +147,28 @@ __global__ __launch_bounds__(256) void append_kernel(
                         vx[j][e] = *reinterpret_cast<const uint32_t*>(src + (8 * (e / 4) + e % 4) * row);
                 }
             }
-            if constexpr (kKeys != kKeysNone) {
+            if constexpr (kKeys == kKeysAsGiven) {
+#pragma unroll
+                for (int j = 0; j < 2 * kSteps; ++j)
+                    piece(j, [&](u32x4& x, int t, int c, int h) __attribute__((always_inline)) {
+                        *reinterpret_cast<u32x4*>(p.k_dst + kd + (c * kstride + t) * 16 + 8 * h) = x;
+                    });
+            }
+            if constexpr (kKeys == kKeysTurned) {
 #pragma unroll
                 for (int j = 0; j < kSteps; ++j) {
                     const int t = lane & 15, c = (lane >> 4) + 4 * j;
-                    if constexpr (kKeys == kKeysTurned) {
-                        float cs8[8], sn8[8];
+                    float cs8[8], sn8[8];
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float u = rope::revolutions(uint32_t(16 * blk + t),
-                                                              make_uint2(p.rope_rho_hi[8 * c + e], p.rope_rho_lo[8 * c + e]));
-                            cs8[e] = __builtin_amdgcn_cosf(u);
-                            sn8[e] = __builtin_amdgcn_sinf(u);
-                        }
-                        const u32x4 x = kx[j], y = ky[j];
-                        kx[j] = rope::rotate_cs(x, y, 0, cs8, sn8);
-                        ky[j] = rope::rotate_cs(y, x, 1, cs8, sn8);
+                    for (int e = 0; e < 8; ++e) {
+                        const float u = rope::revolutions(uint32_t(16 * blk + t),
+                                                          make_uint2(p.rope_rho_hi[8 * c + e], p.rope_rho_lo[8 * c + e]));
+                        cs8[e] = __builtin_amdgcn_cosf(u);
+                        sn8[e] = __builtin_amdgcn_sinf(u);
                     }
+                    const u32x4 x = kx[j], y = ky[j];
+                    kx[j] = rope::rotate_cs(x, y, 0, cs8, sn8);
+                    ky[j] = rope::rotate_cs(y, x, 1, cs8, sn8);
                     if (W || (t >= lo && t < hi)) {
                         uint16_t* dst = p.k_dst + kd + (c * kstride + t) * 16;
                         *reinterpret_cast<u32x4*>(dst) = kx[j];

@@ -137,6 +137,16 @@ __global__ __launch_bounds__(256) void append_kernel(
                     }
                 }
             }
+            // one or two tokens, a decode step's: their values loaded with the keys
+            [[maybe_unused]] const int end = p.zero_tail ? 16 : hi;
+            [[maybe_unused]] uint32_t few[2] = {0u, 0u};
+            if constexpr (kValues && !W) {
+                if (lane < D / 2 && end - lo <= 2) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        if (lo + i < hi) few[i] = *reinterpret_cast<const uint32_t*>(p.v_src + src0 + (lo + i) * row + 2 * lane);
+                }
+            }
             if constexpr (kValues && W) {
 #pragma unroll
                 for (int j = 0; j < kSteps; ++j) {
@@ -193,20 +203,14 @@ __global__ __launch_bounds__(256) void append_kernel(
             }
             if constexpr (kValues && !W) {
                 // 2 dims per lane; slots of token 4 q + i: 8 (q % 2) + 4 (q / 2) + i
-                const int end = p.zero_tail ? 16 : hi;
                 if (lane < D / 2 && end - lo <= 2) {
-                    // one or two tokens, a decode step's
-                    uint32_t x[2] = {0u, 0u};
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        if (lo + i < hi) x[i] = *reinterpret_cast<const uint32_t*>(p.v_src + src0 + (lo + i) * row + 2 * lane);
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         const int t = lo + i;
                         uint16_t* dst = p.v_dst + vd + 32 * lane + 8 * (t % 8 / 4) + 4 * (t / 8) + t % 4;
                         if (t < end) {
-                            dst[0] = uint16_t(x[i]);
-                            dst[16] = uint16_t(x[i] >> 16);
+                            dst[0] = uint16_t(few[i]);
+                            dst[16] = uint16_t(few[i] >> 16);
                         }
                     }
                 } else if (lane < D / 2) {

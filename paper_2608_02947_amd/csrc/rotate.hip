@@ -59,13 +59,14 @@ __global__ __launch_bounds__(256) void rotate_kcache_kernel(const RotateParams p
 //      bytes per token, transposed in registers into two 16-byte stores.  Of a block that
 //      the call does not cover whole only the call's slots are written, so the others keep
 //      their contents (or become zero past the source when zero_tail is set): a lane takes
-//      2 dims, all its tokens loaded first, four tokens at a time where the call has them
-//      (token by token, load and store, 15 tokens in a block of each of 141 x 8 heads
-//      took 23.2 us, and 10.8 so).
+//      2 dims, 8 tokens loaded before the first is stored, four stored at a time where the
+//      call has them (token by token, load and store, 15 tokens in a block of each of 141 x
+//      8 heads took 23.3 us, and 11.0 so; 16 tokens loaded at once need 102 registers for 70, and
+//      16,384 whole tokens then take 34.2 us for 33.2).
 // Bound by HBM; every load of a unit is in flight before the first store.  One thread per
 // (token, chunk) and per (block, dim) with a 64-bit division chain each and 2-byte stores
 // of V, in two launches, took 96 us for 16,384 tokens of 8 heads at d = 128 (134 MB moved,
-// rotated); this takes 33.7 us (4.0 TB/s).
+// rotated); this takes 33.2 us (4.0 TB/s).
 constexpr int kKeysNone = 0, kKeysAsGiven = 1, kKeysTurned = 2;
 
 template <int D, int kKeys, bool kValues, bool kPaged>
@@ -214,28 +215,33 @@ __global__ __launch_bounds__(256) void append_kernel(
                         }
                     }
                 } else if (lane < D / 2) {
-                    uint32_t x[16];
+#pragma unroll 1
+                    for (int h8 = lo & 8; h8 < end; h8 += 8) {
+                        uint32_t x[8];
 #pragma unroll
-                    for (int t = 0; t < 16; ++t) {
-                        x[t] = 0u;
-                        if (t >= lo && t < hi) x[t] = *reinterpret_cast<const uint32_t*>(p.v_src + src0 + t * row + 2 * lane);
-                    }
+                        for (int t = 0; t < 8; ++t) {
+                            x[t] = 0u;
+                            if (h8 + t >= lo && h8 + t < hi)
+                                x[t] = *reinterpret_cast<const uint32_t*>(p.v_src + src0 + (h8 + t) * row + 2 * lane);
+                        }
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        uint16_t* dst = p.v_dst + vd + 32 * lane + 8 * (q % 2) + 4 * (q / 2);
-                        const uint32_t* y = &x[4 * q];
-                        if (4 * q >= lo && 4 * q + 4 <= end) {
-                            *reinterpret_cast<uint2*>(dst) = make_uint2(__builtin_amdgcn_perm(y[1], y[0], 0x05040100u),
-                                                                        __builtin_amdgcn_perm(y[3], y[2], 0x05040100u));
-                            *reinterpret_cast<uint2*>(dst + 16) = make_uint2(__builtin_amdgcn_perm(y[1], y[0], 0x07060302u),
-                                                                             __builtin_amdgcn_perm(y[3], y[2], 0x07060302u));
-                        } else {
+                        for (int q = 0; q < 2; ++q) {
+                            const int t0 = h8 + 4 * q;  // its slots: 8 q + h8 / 2 on
+                            uint16_t* dst = p.v_dst + vd + 32 * lane + 8 * q + h8 / 2;
+                            const uint32_t* y = &x[4 * q];
+                            if (t0 >= lo && t0 + 4 <= end) {
+                                *reinterpret_cast<uint2*>(dst) = make_uint2(__builtin_amdgcn_perm(y[1], y[0], 0x05040100u),
+                                                                            __builtin_amdgcn_perm(y[3], y[2], 0x05040100u));
+                                *reinterpret_cast<uint2*>(dst + 16) = make_uint2(__builtin_amdgcn_perm(y[1], y[0], 0x07060302u),
+                                                                                 __builtin_amdgcn_perm(y[3], y[2], 0x07060302u));
+                            } else {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                if (4 * q + i >= lo && 4 * q + i < end) {
-                                    dst[i] = uint16_t(y[i]);
-                                    dst[16 + i] = uint16_t(y[i] >> 16);
-                                }
+                                for (int i = 0; i < 4; ++i)
+                                    if (t0 + i >= lo && t0 + i < end) {
+                                        dst[i] = uint16_t(y[i]);
+                                        dst[16 + i] = uint16_t(y[i] >> 16);
+                                    }
+                            }
                         }
                     }
                 }
